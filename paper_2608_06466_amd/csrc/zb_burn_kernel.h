@@ -622,12 +622,13 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
     if (WANTJ) {
         // clear the Jacobian rows this lane owns (the row walk below adds into them) and its
         // species' entries of the T row (the reactions add into those; the T row's T entry is
-        // written whole)
+        // written whole).  Without temperature there is no T row: with ns = NVP its place is the
+        // next zone's area.
         sfor<0, RPL>([&](auto S) {
             int i = row_of<NVP, L>(c, S);
             if (i < N.ns) {
                 sfor<0, NVP>([&](auto J) { jb[i * JS + J] = JT(0); });
-                jb[N.ns * JS + i] = JT(0);
+                if (N.thermal) jb[N.ns * JS + i] = JT(0);
             }
         });
     }
