@@ -275,6 +275,10 @@ __device__ __forceinline__ unsigned bcast_k32(unsigned v)
 template <int L, int K>
 __device__ __forceinline__ double bcast_k(double v)
 {
+    if constexpr (L == 16) {   // row_newbcast is the one DPP pattern 64-bit moves take
+        const long long r = __builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + K, 0xF, 0xF, false);
+        return __longlong_as_double(r);
+    }
     unsigned long long u = (unsigned long long)__double_as_longlong(v);
     unsigned lo = bcast_k32<L, K>((unsigned)(u & 0xffffffffu));
     unsigned hi = bcast_k32<L, K>((unsigned)(u >> 32));
@@ -881,6 +885,226 @@ __device__ __forceinline__ void steps8(int nv, F &&f)
     });
 }
 
+// ------------------------------------------- triangular solves, one row a lane
+// Lane masks of the wave for groups of L lanes (L >= 16), the lanes of each group taken as
+// 16-lane blocks (DPP rows) in which a step broadcasts by row_newbcast.
+template <int L>
+constexpr unsigned long long group_lanes(unsigned long long m)
+{
+    for (int w = L; w < 64; w *= 2) m |= m << w;
+    return m;
+}
+// lanes a..b of each group
+template <int L>
+constexpr unsigned long long lanes_in(int a, int b)
+{
+    return group_lanes<L>((b - a == 63) ? ~0ull : (((1ull << (b - a + 1)) - 1ull) << a));
+}
+
+// Value of the 16-lane block B of the group in every block, lane by lane.
+template <int L, int B>
+__device__ __forceinline__ unsigned bcast_block32(unsigned v)
+{
+    unsigned a, b;
+    if constexpr (L >= 32) {
+        xswap<16>(v, a, b);
+        v = (B & 1) ? b : a;
+    }
+    if constexpr (L == 64) {
+        xswap<32>(v, a, b);
+        v = (B >> 1) ? b : a;
+    }
+    return v;
+}
+template <int L, int B>
+__device__ __forceinline__ float bcast_block(float v)
+{
+    return __uint_as_float(bcast_block32<L, B>(__float_as_uint(v)));
+}
+template <int L, int B>
+__device__ __forceinline__ double bcast_block(double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = bcast_block32<L, B>((unsigned)u), hi = bcast_block32<L, B>((unsigned)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Steps of the solves, written out: v += dpp(v) * (-m) is one v_fmac with row_newbcast, but the
+// compiler keeps the broadcast, the product's select and a compare of the lane apart (5 and 6
+// vector instructions a step in FP32, 7 and 8 in FP64).  Here EXEC, not a select, keeps the lanes
+// that a step does not reach, so a forward step is one vector instruction and a backward one two;
+// the rest is scalar.  The masks are ANDed with the EXEC found, so groups that are switched off
+// stay off.  Wait states: a VALU write needs two before DPP reads it (the two s_and), and the
+// block ends with more than any later reader of v needs.  Burns with these solves, before and
+// after, bitwise the same: 14 variables FP64 (50021 zones) 144.7 -> 135.0 ms, mixed (2^18) 570 ->
+// 549 ms, with Jacobian reuse (30011, mixed) 85.7 -> 76.8 ms; 22 variables FP64 (20011) 152 -> 136
+// ms, mixed (40009) 178 -> 162 ms.
+#define ZB_EXEC_SAVE "s_mov_b32 %[el], exec_lo\n s_mov_b32 %[eh], exec_hi\n"
+#define ZB_EXEC_BACK "s_mov_b32 exec_lo, %[el]\n s_mov_b32 exec_hi, %[eh]\n s_nop 1\n"
+#define ZB_EXEC_AND(i) "s_and_b32 exec_lo, %[el], %[x" #i "]\n s_and_b32 exec_hi, %[eh], %[y" #i "]\n"
+#define ZB_FMAC(T, src, m, l) "v_fmac_" T "_dpp %[v], " src ", -" m " row_newbcast:" l " row_mask:0xf bank_mask:0xf\n"
+#define ZB_FWD(T, i) ZB_EXEC_AND(i) ZB_FMAC(T, "%[v]", "%[m" #i "]", "%[l" #i "]")
+#define ZB_BWD(T, i) "v_mul_" T " %[t], %[v], %[d]\n" ZB_EXEC_AND(i) ZB_FMAC(T, "%[t]", "%[m" #i "]", "%[l" #i "]")
+#define ZB_OFF(T, i) ZB_FMAC(T, "%[t]", "%[m" #i "]", "%[l" #i "]")
+// operands of step i: the multiplier, the lanes it reaches, the broadcast lane
+#define ZB_OP(i) [m##i] "v"(m[k(i)]), [x##i] "i"((int)(unsigned)mask(k(i))), \
+                 [y##i] "i"((int)(unsigned)(mask(k(i)) >> 32)), [l##i] "i"(k(i) % 16)
+#define ZB_OPO(i) [m##i] "v"(m[k(i)]), [l##i] "i"(k(i) % 16)
+
+// Forward steps A .. A+N-1 within their 16-lane block: v_i -= M_ik v_k for the block's lanes
+// i > k.  Lane k itself is among the lanes (the broadcast reads it) with M_kk = 0.
+template <int L, int A, int N, class LT>
+__device__ __forceinline__ void fwd_steps(LT &v, const LT *m)
+{
+    constexpr auto k = [](int i) constexpr { return A + i; };
+    constexpr auto mask = [](int kk) constexpr { return lanes_in<L>(kk, kk | 15); };
+    int el, eh;
+    if constexpr (sizeof(LT) == 4 && N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_FWD("f32", 0) ZB_FWD("f32", 1) ZB_FWD("f32", 2) ZB_FWD("f32", 3)
+                     ZB_FWD("f32", 4) ZB_FWD("f32", 5) ZB_FWD("f32", 6) ZB_FWD("f32", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5), ZB_OP(6), ZB_OP(7) : "scc");
+    else if constexpr (sizeof(LT) == 4)
+        asm volatile(ZB_EXEC_SAVE ZB_FWD("f32", 0) ZB_FWD("f32", 1) ZB_FWD("f32", 2) ZB_FWD("f32", 3)
+                     ZB_FWD("f32", 4) ZB_FWD("f32", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5) : "scc");
+    else if constexpr (N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_FWD("f64", 0) ZB_FWD("f64", 1) ZB_FWD("f64", 2) ZB_FWD("f64", 3)
+                     ZB_FWD("f64", 4) ZB_FWD("f64", 5) ZB_FWD("f64", 6) ZB_FWD("f64", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5), ZB_OP(6), ZB_OP(7) : "scc");
+    else
+        asm volatile(ZB_EXEC_SAVE ZB_FWD("f64", 0) ZB_FWD("f64", 1) ZB_FWD("f64", 2) ZB_FWD("f64", 3)
+                     ZB_FWD("f64", 4) ZB_FWD("f64", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5) : "scc");
+    static_assert(N == 8 || N == 6, "steps of a block");
+}
+
+// Backward steps A+N-1 .. A within their block: v_i -= M_ik (v_k / U_kk) for its lanes i < k.
+template <int L, int A, int N, class LT>
+__device__ __forceinline__ void bwd_steps(LT &v, const LT *m, LT d)
+{
+    constexpr auto k = [](int i) constexpr { return A + N - 1 - i; };
+    constexpr auto mask = [](int kk) constexpr { return lanes_in<L>(kk & ~15, kk); };
+    int el, eh;
+    LT t;
+    if constexpr (sizeof(LT) == 4 && N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_BWD("f32", 0) ZB_BWD("f32", 1) ZB_BWD("f32", 2) ZB_BWD("f32", 3)
+                     ZB_BWD("f32", 4) ZB_BWD("f32", 5) ZB_BWD("f32", 6) ZB_BWD("f32", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh), [t] "=&v"(t)
+                     : [d] "v"(d), ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5), ZB_OP(6), ZB_OP(7) : "scc");
+    else if constexpr (sizeof(LT) == 4)
+        asm volatile(ZB_EXEC_SAVE ZB_BWD("f32", 0) ZB_BWD("f32", 1) ZB_BWD("f32", 2) ZB_BWD("f32", 3)
+                     ZB_BWD("f32", 4) ZB_BWD("f32", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh), [t] "=&v"(t)
+                     : [d] "v"(d), ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5) : "scc");
+    else if constexpr (N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_BWD("f64", 0) ZB_BWD("f64", 1) ZB_BWD("f64", 2) ZB_BWD("f64", 3)
+                     ZB_BWD("f64", 4) ZB_BWD("f64", 5) ZB_BWD("f64", 6) ZB_BWD("f64", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh), [t] "=&v"(t)
+                     : [d] "v"(d), ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5), ZB_OP(6), ZB_OP(7) : "scc");
+    else
+        asm volatile(ZB_EXEC_SAVE ZB_BWD("f64", 0) ZB_BWD("f64", 1) ZB_BWD("f64", 2) ZB_BWD("f64", 3)
+                     ZB_BWD("f64", 4) ZB_BWD("f64", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh), [t] "=&v"(t)
+                     : [d] "v"(d), ZB_OP(0), ZB_OP(1), ZB_OP(2), ZB_OP(3), ZB_OP(4), ZB_OP(5) : "scc");
+    static_assert(N == 8 || N == 6, "steps of a block");
+}
+
+// N steps from k = A (descending from A+N-1 with REV) for the lanes R0..R1 of the group, which
+// lie in other blocks: t holds the steps' values in every block.
+template <int L, int A, int N, bool REV, int R0, int R1, class LT>
+__device__ __forceinline__ void off_steps(LT &v, const LT *m, LT t)
+{
+    constexpr auto k = [](int i) constexpr { return REV ? A + N - 1 - i : A + i; };
+    constexpr unsigned long long mk = lanes_in<L>(R0, R1);
+    int el, eh;
+    if constexpr (sizeof(LT) == 4 && N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_EXEC_AND(0) ZB_OFF("f32", 0) ZB_OFF("f32", 1) ZB_OFF("f32", 2)
+                     ZB_OFF("f32", 3) ZB_OFF("f32", 4) ZB_OFF("f32", 5) ZB_OFF("f32", 6) ZB_OFF("f32", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : [t] "v"(t), [x0] "i"((int)(unsigned)mk), [y0] "i"((int)(unsigned)(mk >> 32)), ZB_OPO(0),
+                       ZB_OPO(1), ZB_OPO(2), ZB_OPO(3), ZB_OPO(4), ZB_OPO(5), ZB_OPO(6), ZB_OPO(7) : "scc");
+    else if constexpr (sizeof(LT) == 4)
+        asm volatile(ZB_EXEC_SAVE ZB_EXEC_AND(0) ZB_OFF("f32", 0) ZB_OFF("f32", 1) ZB_OFF("f32", 2)
+                     ZB_OFF("f32", 3) ZB_OFF("f32", 4) ZB_OFF("f32", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : [t] "v"(t), [x0] "i"((int)(unsigned)mk), [y0] "i"((int)(unsigned)(mk >> 32)), ZB_OPO(0),
+                       ZB_OPO(1), ZB_OPO(2), ZB_OPO(3), ZB_OPO(4), ZB_OPO(5) : "scc");
+    else if constexpr (N == 8)
+        asm volatile(ZB_EXEC_SAVE ZB_EXEC_AND(0) ZB_OFF("f64", 0) ZB_OFF("f64", 1) ZB_OFF("f64", 2)
+                     ZB_OFF("f64", 3) ZB_OFF("f64", 4) ZB_OFF("f64", 5) ZB_OFF("f64", 6) ZB_OFF("f64", 7) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : [t] "v"(t), [x0] "i"((int)(unsigned)mk), [y0] "i"((int)(unsigned)(mk >> 32)), ZB_OPO(0),
+                       ZB_OPO(1), ZB_OPO(2), ZB_OPO(3), ZB_OPO(4), ZB_OPO(5), ZB_OPO(6), ZB_OPO(7) : "scc");
+    else
+        asm volatile(ZB_EXEC_SAVE ZB_EXEC_AND(0) ZB_OFF("f64", 0) ZB_OFF("f64", 1) ZB_OFF("f64", 2)
+                     ZB_OFF("f64", 3) ZB_OFF("f64", 4) ZB_OFF("f64", 5) ZB_EXEC_BACK
+                     : [v] "+v"(v), [el] "=&s"(el), [eh] "=&s"(eh)
+                     : [t] "v"(t), [x0] "i"((int)(unsigned)mk), [y0] "i"((int)(unsigned)(mk >> 32)), ZB_OPO(0),
+                       ZB_OPO(1), ZB_OPO(2), ZB_OPO(3), ZB_OPO(4), ZB_OPO(5) : "scc");
+    static_assert(N == 8 || N == 6, "steps of a block");
+}
+#undef ZB_OP
+#undef ZB_OPO
+#undef ZB_OFF
+#undef ZB_BWD
+#undef ZB_FWD
+#undef ZB_FMAC
+#undef ZB_EXEC_AND
+#undef ZB_EXEC_BACK
+#undef ZB_EXEC_SAVE
+
+// Where tri_solve runs: one row a lane in groups of 16 lanes or more, but for the whole-wave FP32
+// solve, which reads a step's value with one v_readlane (nv 48, 16384 zones mixed: 372 ms so, 380
+// in blocks; FP64, two v_readlane a value, 8192 zones: 271 ms so, 259 in blocks).
+template <int L, class LT>
+constexpr bool dpp_solve() { return L >= 16 && !(L == 64 && sizeof(LT) == 4); }
+
+// L U x = v with the factors' row i in lane i (M_ii = 0, d = 1 / U_ii): v comes back as U_ii x_i,
+// every sum taken in the order of the plain loops.  The blocks of 16 rows in turn: the steps
+// within a block, then its values brought to the other blocks (permlane swaps) and subtracted
+// there, so that no step needs a lane outside its DPP row.  nv is tested once per 8 steps, as in
+// steps8.
+template <int NVP, int L, class LT>
+__device__ __forceinline__ void tri_solve(int nv, LT &v, const LT (&m)[NVP], LT d)
+{
+    constexpr int NB = (NVP + 15) / 16;
+    sfor<0, NB>([&](auto B) {
+        constexpr int b = B, a = 16 * b, e = (a + 16 < NVP) ? a + 16 : NVP;
+        sfor<0, (e - a + 7) / 8>([&](auto C) {
+            constexpr int k0 = a + 8 * C, n = (k0 + 8 < e) ? 8 : e - k0;
+            if (k0 < nv) fwd_steps<L, k0, n>(v, m);
+        });
+        if constexpr (b + 1 < NB) {
+            if (e < nv) {
+                const LT t = bcast_block<L, b>(v);
+                off_steps<L, a, 8, false, e, L - 1>(v, m, t);
+                off_steps<L, a + 8, 8, false, e, L - 1>(v, m, t);
+            }
+        }
+    });
+    sfor<0, NB>([&](auto B) {
+        constexpr int b = NB - 1 - B, a = 16 * b, e = (a + 16 < NVP) ? a + 16 : NVP;
+        constexpr int nc = (e - a + 7) / 8;
+        if (a < nv) {
+            sfor<0, nc>([&](auto C) {
+                constexpr int k0 = a + 8 * (nc - 1 - C), n = (k0 + 8 < e) ? 8 : e - k0;
+                if (k0 < nv) bwd_steps<L, k0, n>(v, m, d);
+            });
+            if constexpr (b > 0) {
+                const LT t = bcast_block<L, b>(v * d);
+                if constexpr (nc == 2) {
+                    if (a + 8 < nv) off_steps<L, a + 8, e - a - 8, true, 0, a - 1>(v, m, t);
+                }
+                off_steps<L, a, (e - a < 8) ? e - a : 8, true, 0, a - 1>(v, m, t);
+            }
+        }
+    });
+}
+
 typedef float zb_v16f __attribute__((ext_vector_type(16)));
 typedef float zb_v4f __attribute__((ext_vector_type(4)));
 
@@ -1050,7 +1274,10 @@ __device__ __forceinline__ void lu_factor_blocked(const Ctx &c, Zone<NVP, L, LT>
     });
     // pivot row k to lane k, as in lu_factor
     const int src = z.pivlane;
-    sfor<0, NVP>([&](auto J) { z.M[0][J] = gather(z.M[0][J], src); });
+    sfor<0, NVP>([&](auto J) {
+            const LT mj = gather(z.M[0][J], src);
+            z.M[0][J] = (J == c.gl) ? LT(0) : mj;   // the pivots' places are 0 (tri_solve)
+        });
     z.dinv[0] = gather(z.dinv[0], src);
     z.rs[0] = gather(z.rs[0], src);
 }
@@ -1181,7 +1408,10 @@ __device__ __forceinline__ void lu_factor(const Ctx &c, Zone<NVP, L, LT> &z)
         // Move pivot row k to group lane k: the factors become those of P M in natural
         // order, and the triangular solves broadcast from a fixed lane.
         const int src = (int)(threadIdx.x & (64 - L)) + z.pivlane;
-        sfor<0, NVP>([&](auto J) { z.M[0][J] = gather(z.M[0][J], src); });
+        sfor<0, NVP>([&](auto J) {
+            const LT mj = gather(z.M[0][J], src);
+            z.M[0][J] = (J == c.gl) ? LT(0) : mj;   // the pivots' places are 0 (tri_solve)
+        });
         z.dinv[0] = gather(z.dinv[0], src);
         if constexpr (sizeof(LT) == 4) z.rs[0] = gather(z.rs[0], src);
     }
@@ -1212,7 +1442,7 @@ __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
         if (c.gl == k) z.dinv[0] = rinv;
         const bool act = c.gl > k;
         const LT l = act ? z.M[0][k] * rinv : LT(0);
-        if (act) z.M[0][k] = l;
+        if (c.gl >= k) z.M[0][k] = l;   // the pivot's own place is 0 (tri_solve)
         sfor<k + 1, NVP>([&](auto J) { z.M[0][J] = fma(-l, bcast_k<L, k>(z.M[0][J]), z.M[0][J]); });
     });
     return !gany<L>(bad);
@@ -1247,16 +1477,20 @@ __device__ __forceinline__ void lu_solve(const Ctx &c, const Zone<NVP, L, LT> &z
         const int src = (int)(threadIdx.x & (64 - L)) + z.pivlane;
         const double bp = gather(b[0], src);
         LT v = MIXED ? (LT)(bp * (double)z.rs[0]) : (LT)bp;
-        steps8<NVP>(nv, [&](auto K) {
-            constexpr int k = K;
-            const LT yk = bcast_k<L, k>(v);
-            if (after(c.gl, v) > k) v = fma(-z.M[0][k], yk, v);
-        });
-        steps8<NVP, true>(nv, [&](auto K) {
-            constexpr int k = K;
-            const LT xk = bcast_k<L, k>(v * z.dinv[0]);
-            if (after(c.gl, v) < k) v = fma(-z.M[0][k], xk, v);
-        });
+        if constexpr (dpp_solve<L, LT>()) {
+            tri_solve<NVP, L>(nv, v, z.M[0], z.dinv[0]);
+        } else {
+            steps8<NVP>(nv, [&](auto K) {
+                constexpr int k = K;
+                const LT yk = bcast_k<L, k>(v);
+                if (after(c.gl, v) > k) v = fma(-z.M[0][k], yk, v);
+            });
+            steps8<NVP, true>(nv, [&](auto K) {
+                constexpr int k = K;
+                const LT xk = bcast_k<L, k>(v * z.dinv[0]);
+                if (after(c.gl, v) < k) v = fma(-z.M[0][k], xk, v);
+            });
+        }
         double x = c.gl < nv ? (double)(v * z.dinv[0]) : 0.0;
         if (MIXED) x *= z.cs[0];
         b[0] = x;
