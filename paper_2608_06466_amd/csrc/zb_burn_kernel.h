@@ -1427,14 +1427,217 @@ __device__ __forceinline__ void lu_factor(const Ctx &c, Zone<NVP, L, LT> &z)
 // solutions are the same for every pivot order.
 constexpr float PIV_KEEP = 0.5f;
 
+// Whether this lane is in the wave mask m (a constant), as a scalar mask made where it is used:
+// a compare of the lane number would be shared between steps and spilled to vector registers.
+__device__ __forceinline__ bool lane_in(unsigned long long m)
+{
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+// d_j -= l p_j for N columns, p_j taken from lane K % 16 of the lane's own 16-lane row: one
+// v_fmac with row_newbcast a column.  The compiler makes a broadcast and an FMA of it (two vector
+// instructions in FP32; in FP64, where it moves the halves apart, three).  The leading wait
+// states are those a DPP read of freshly written registers needs; within a block no
+// instruction reads what another wrote (own: p is d, each lane's column read before it is
+// written).  14 variables with it in the LU: FP64 (50021 zones) 135.0 -> 132.1 ms, mixed (2^18)
+// 549 -> 539 ms.
+#define ZB_UPD(T, j) "v_fmac_" T "_dpp %[d" #j "], %[p" #j "], -%[l] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n"
+#define ZB_UPS(T, j) "v_fmac_" T "_dpp %[d" #j "], %[d" #j "], -%[l] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n"
+#define ZB_D(j) [d##j] "+v"(d[j])
+#define ZB_P(j) [p##j] "v"(p[j])
+#define ZB_UPDATE(T)                                                                                       \
+    if constexpr (N == 4 && OWN)                                                                           \
+        asm("s_nop 1\n" ZB_UPS(T, 0) ZB_UPS(T, 1) ZB_UPS(T, 2) ZB_UPS(T, 3)                               \
+            : ZB_D(0), ZB_D(1), ZB_D(2), ZB_D(3) : [l] "v"(l), [k] "i"(K % 16));                           \
+    else if constexpr (N == 2 && OWN)                                                                      \
+        asm("s_nop 1\n" ZB_UPS(T, 0) ZB_UPS(T, 1) : ZB_D(0), ZB_D(1) : [l] "v"(l), [k] "i"(K % 16));      \
+    else if constexpr (OWN)                                                                                \
+        asm("s_nop 1\n" ZB_UPS(T, 0) : ZB_D(0) : [l] "v"(l), [k] "i"(K % 16));                            \
+    else if constexpr (N == 4)                                                                             \
+        asm("s_nop 1\n" ZB_UPD(T, 0) ZB_UPD(T, 1) ZB_UPD(T, 2) ZB_UPD(T, 3)                               \
+            : ZB_D(0), ZB_D(1), ZB_D(2), ZB_D(3)                                                           \
+            : ZB_P(0), ZB_P(1), ZB_P(2), ZB_P(3), [l] "v"(l), [k] "i"(K % 16));                            \
+    else if constexpr (N == 2)                                                                             \
+        asm("s_nop 1\n" ZB_UPD(T, 0) ZB_UPD(T, 1)                                                         \
+            : ZB_D(0), ZB_D(1) : ZB_P(0), ZB_P(1), [l] "v"(l), [k] "i"(K % 16));                           \
+    else                                                                                                   \
+        asm("s_nop 1\n" ZB_UPD(T, 0) : ZB_D(0) : ZB_P(0), [l] "v"(l), [k] "i"(K % 16));
+template <int K, int N, bool OWN, class LT>
+__device__ __forceinline__ void row_update_n(LT *d, const LT *p, LT l)
+{
+    if constexpr (sizeof(LT) == 4) { ZB_UPDATE("f32") } else { ZB_UPDATE("f64") }
+}
+#undef ZB_UPDATE
+#undef ZB_P
+#undef ZB_D
+#undef ZB_UPS
+#undef ZB_UPD
+
+template <int K, int B, int E, bool OWN, class LT>
+__device__ __forceinline__ void row_update(LT *d, const LT *p, LT l)
+{
+    if constexpr (E - B >= 4) {
+        row_update_n<K, 4, OWN>(d + B, p + B, l);
+        row_update<K, B + 4, E, OWN>(d, p, l);
+    } else if constexpr (E - B >= 2) {
+        row_update_n<K, 2, OWN>(d + B, p + B, l);
+        row_update<K, B + 2, E, OWN>(d, p, l);
+    } else if constexpr (E - B == 1) {
+        row_update_n<K, 1, OWN>(d + B, p + B, l);
+    }
+}
+
+// 4 x 4 (L = 64) or 2 x 2 (L = 32) transpose of registers against the group's 16-lane rows: x[c]
+// of lane row s becomes x[s] of lane row c.  Its own inverse.
+template <int D>
+__device__ __forceinline__ void swap_rows(float &a, float &b)
+{
+    auto sw = [](unsigned u, unsigned v) {
+        if constexpr (D == 16) return __builtin_amdgcn_permlane16_swap(u, v, false, false);
+        else return __builtin_amdgcn_permlane32_swap(u, v, false, false);
+    };
+    const auto r = sw(__float_as_uint(a), __float_as_uint(b));
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+template <int D>
+__device__ __forceinline__ void swap_rows(double &a, double &b)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(a),
+                             v = (unsigned long long)__double_as_longlong(b);
+    float al = __uint_as_float((unsigned)u), ah = __uint_as_float((unsigned)(u >> 32));
+    float bl = __uint_as_float((unsigned)v), bh = __uint_as_float((unsigned)(v >> 32));
+    swap_rows<D>(al, bl);
+    swap_rows<D>(ah, bh);
+    a = __longlong_as_double((long long)(((unsigned long long)__float_as_uint(ah) << 32) | __float_as_uint(al)));
+    b = __longlong_as_double((long long)(((unsigned long long)__float_as_uint(bh) << 32) | __float_as_uint(bl)));
+}
+template <int L, class LT>
+__device__ __forceinline__ void transpose_rows(LT *x)
+{
+    if constexpr (L == 32) {
+        swap_rows<16>(x[0], x[1]);
+    } else {
+        swap_rows<16>(x[0], x[1]);
+        swap_rows<16>(x[2], x[3]);
+        swap_rows<32>(x[0], x[2]);
+        swap_rows<32>(x[1], x[3]);
+    }
+}
+
+// The kept-order LU of groups of 32 and 64 lanes, spread over both dimensions: lane i of 16-lane
+// row r holds the columns c = r (mod C) of the matrix rows i, i + 16, ... (C = L / 16 rows of
+// lanes), so that every pivot row it needs is in its own 16-lane row and an update is one
+// v_fmac a column, where with a row a lane each pivot element has to cross the rows of lanes
+// first (nv 22: a DPP move, a copy and a swap of two issue slots a 32-bit half; nv 48: a
+// v_readlane a half).  The C columns that start a step are brought to every row of lanes at once
+// and factored there by all of them.  Every element takes the same operations in the same order
+// as with a row a lane: the factors are the same bits.  The rows come and go by permlane swaps
+// (transpose_rows).
+template <int NVP, int L, class LT>
+__device__ __forceinline__ bool lu_kept_spread(const Ctx &c, Zone<NVP, L, LT> &z)
+{
+    constexpr int C = L / 16, NJ = NVP / C, S = (NVP + 15) / 16;
+    static_assert(NVP % C == 0 && S <= C, "columns in whole sets");
+    const int nv = own_copy(c.nv);
+    LT Y[S][NJ];
+    sfor<0, NJ>([&](auto J) {
+        LT x[C];
+        sfor<0, C>([&](auto R) { x[R] = z.M[0][C * J + R]; });
+        transpose_rows<L>(x);
+        sfor<0, S>([&](auto R) { Y[R][J] = x[R]; });
+    });
+    unsigned long long bad = 0;
+    auto panel = [&](auto P) {
+        constexpr int p = P, k0 = C * p, sk = k0 / 16;
+        // the panel's columns, of the rows from the pivot's 16-row block on, in every lane row
+        LT X[S][C];
+        sfor<sk, S>([&](auto R) {
+            X[R][0] = X[R][1] = Y[R][p];
+            swap_rows<16>(X[R][0], X[R][1]);
+            if constexpr (C == 4) {
+                X[R][2] = X[R][0];
+                X[R][3] = X[R][1];
+                swap_rows<32>(X[R][0], X[R][2]);
+                swap_rows<32>(X[R][1], X[R][3]);
+            }
+        });
+        sfor<0, C>([&](auto Q) {
+            constexpr int q = Q, k = k0 + q, kl = k % 16;
+            const LT piv = bcast_k<16, kl>(X[sk][q]);
+            const bool gt = lane_in(group_lanes<16>((0xFFFEull << kl) & 0xFFFFull));
+            const bool ge = lane_in(group_lanes<16>((0xFFFFull << kl) & 0xFFFFull));
+            const LT lim = fabs(piv) * LT(1.0f / PIV_KEEP);
+            sfor<sk, S>([&](auto R) {
+                const bool b = !(fabs(X[R][q]) <= lim);
+                bad |= __builtin_amdgcn_ballot_w64(b) &
+                       (R == sk ? group_lanes<16>((0xFFFEull << kl) & 0xFFFFull) : ~0ull);
+            });
+            const LT rinv = recip(piv);
+            if (lane_in(group_lanes<L>(1ull << k))) z.dinv[0] = rinv;
+            sfor<sk, S>([&](auto R) {
+                constexpr int r = R;
+                LT l = X[r][q] * rinv;
+                if constexpr (r == sk) {
+                    l = gt ? l : LT(0);
+                    X[r][q] = ge ? l : X[r][q];   // the pivot's own place is 0 (tri_solve)
+                } else {
+                    X[r][q] = l;
+                }
+                // rows below first: they read the pivot's block before its own update
+            });
+            sfor<0, S - sk>([&](auto RR) {
+                constexpr int r = S - 1 - RR;
+                LT l = X[r][q];
+                if constexpr (r == sk) l = gt ? l : LT(0);
+                row_update<k, q + 1, C, (r == sk)>(X[r], X[sk], l);
+                row_update<k, p + 1, NJ, (r == sk)>(Y[r], Y[sk], l);
+            });
+        });
+        sfor<sk, S>([&](auto R) {
+            LT v = X[R][0];
+            sfor<1, C>([&](auto Q) { v = lane_in(lanes_in<L>(16 * Q, 16 * Q + 15)) ? X[R][Q] : v; });
+            Y[R][p] = v;
+        });
+    };
+    // nv tested once per 8 steps, as in steps8
+    sfor<0, (NJ * C + 7) / 8>([&](auto G) {
+        constexpr int a = 8 / C * G, b = (8 / C * G + 8 / C < NJ) ? 8 / C * G + 8 / C : NJ;
+        if (a * C < nv) sfor<a, b>(panel);
+    });
+    sfor<0, NJ>([&](auto J) {
+        LT x[C];
+        sfor<0, C>([&](auto R) {
+            if constexpr (R < S) x[R] = Y[R][J];
+            else x[R] = LT(0);
+        });
+        transpose_rows<L>(x);
+        sfor<0, C>([&](auto R) { z.M[0][C * J + R] = x[R]; });
+    });
+    return !gany<L>(lane_in(bad));
+}
+
 template <int NVP, int L, class LT>
 __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
 {
+    if constexpr (L >= 32) return lu_kept_spread(c, z);
     const int nv = own_copy(c.nv);
     bool bad = false;
     steps8<NVP>(nv, [&](auto K) {
         constexpr int k = K;
         const LT piv = bcast_k<L, k>(z.M[0][k]);
+        if constexpr (L == 16) {
+            const bool gt = lane_in(group_lanes<L>((0xFFFEull << k) & 0xFFFFull));
+            const bool ge = lane_in(group_lanes<L>((0xFFFFull << k) & 0xFFFFull));
+            bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
+            const LT rinv = recip(piv);
+            if (lane_in(group_lanes<L>(1ull << k))) z.dinv[0] = rinv;
+            LT l = z.M[0][k] * rinv;
+            l = gt ? l : LT(0);
+            z.M[0][k] = ge ? l : z.M[0][k];   // the pivot's own place is 0 (tri_solve)
+            row_update<k, k + 1, NVP, true>(z.M[0], z.M[0], l);
+            return;
+        }
         // each candidate against the pivot in its own lane, so no reduction per step: the
         // rows of lanes below k are eliminated, lanes past nvp hold zero rows (a NaN fails)
         if (c.gl > k) bad = bad || !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP));
@@ -1442,7 +1645,7 @@ __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
         if (c.gl == k) z.dinv[0] = rinv;
         const bool act = c.gl > k;
         const LT l = act ? z.M[0][k] * rinv : LT(0);
-        if (c.gl >= k) z.M[0][k] = l;   // the pivot's own place is 0 (tri_solve)
+        if (act) z.M[0][k] = l;
         sfor<k + 1, NVP>([&](auto J) { z.M[0][J] = fma(-l, bcast_k<L, k>(z.M[0][J]), z.M[0][J]); });
     });
     return !gany<L>(bad);
