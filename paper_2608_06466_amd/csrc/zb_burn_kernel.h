@@ -75,6 +75,10 @@ __device__ __forceinline__ int4 gload(const int4 *p)
     const zb_v4i v = *(const __attribute__((address_space(1))) zb_v4i *)p;
     return make_int4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ unsigned gload(const unsigned *p)
+{
+    return *(const __attribute__((address_space(1))) unsigned *)p;
+}
 __device__ __forceinline__ double4 gload(const double4 *p)
 {
     const __attribute__((address_space(1))) zb_v2d *q = (const __attribute__((address_space(1))) zb_v2d *)p;
@@ -575,8 +579,14 @@ __device__ __forceinline__ double wrms(const Ctx &c, const Zone<NVP, L, LT> &z,
 
 // ------------------------------------------------------------- network
 
-// f(y) for the group's zone; with WANTJ also assembles M = I - gamma J (and
-// its FP32 scaling) in registers.  y and f are by local row.
+// f(y) for the group's zone; with WANTJ also the Jacobian rows in LDS.  y and f are by local row.
+//
+// An evaluation is half of a step attempt, bound by instructions and, with few waves, by the
+// latency of the network tables.  So the tables are small and decoded where they are read (a
+// packed word per reaction and per list entry, four entries a 16-byte load), the first reaction
+// of each lane and the 14-row kernels' whole lists are requested before the temperature's
+// logarithm, and the row walks have no branches: padding entries name a slot past the reactions
+// that holds 0 in every column (zone_start).
 template <bool WANTJ, int NVP, int L, class LT>
 __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const double (&yv)[Zone<NVP, L, LT>::RPL],
                      double (&fo)[Zone<NVP, L, LT>::RPL])
@@ -588,22 +598,30 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
     double *rx = c.S + c.lay.rx;
     using JT = JacT<NVP, LT>;
     JT *jb = (JT *)(c.S + c.lay.jbuf);
+    const int nr = N.nr;
+    // byte offset into an LDS array
+    auto at = [](auto *p, int off) { return (decltype(p))((char *)p + off); };
 
-    // The 14-row kernels with a Jacobian every step (one row a lane, registers to spare): a
-    // row's whole list, up to 6 entry pairs, is loaded first, so its latency overlaps the
-    // rate evaluation, and walked from registers.  Elsewhere the extra registers cost
-    // occupancy or spills, and the list is streamed.
-    constexpr int PMAX = (RPL == 1 && NVP == 14 && L == 16) ? 6 : 0;
-    int4 pre[PMAX > 0 ? PMAX : 1];
-    const int n2 = N.inv_len / 2;
-    const bool use_pre = PMAX > 0 && c.jac_policy == 0 && n2 <= PMAX;
-    if constexpr (PMAX > 0) {
+    // The 14-row kernels (one row a lane): a row's whole list, up to three loads of four
+    // entries, is requested here.  Elsewhere the list is streamed.
+    constexpr int QMX = (RPL == 1 && NVP == 14 && L == 16) ? 3 : 0;
+    int4 pre[QMX > 0 ? QMX : 1];
+    const int n4 = N.inv_len / 4;
+    const bool use_pre = QMX > 0 && n4 <= QMX;
+    if constexpr (QMX > 0) {
         const int i0 = row_of<NVP, L>(c, 0);
         const int4 *l0 = (const int4 *)(N.inv + (i0 < N.ns ? i0 : 0) * N.inv_len);
-        sfor<0, PMAX>([&](auto P) {
+        sfor<0, QMX>([&](auto P) {
             pre[P] = make_int4(0, 0, 0, 0);
-            if (use_pre && P < n2) pre[P] = gload(l0 + P);
+            if (use_pre && P < n4) pre[P] = gload(l0 + P);
         });
+    }
+    unsigned nab = 0;
+    double4 npr = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (nr > 0) {
+        const int r = c.gl < nr ? c.gl : nr - 1;
+        nab = gload(N.rct + r);
+        npr = gload(N.par + r);
     }
     // one row a lane: T from its lane through the LDS crossbar, so that its logarithm and
     // reciprocal overlap the stores below instead of waiting for them
@@ -622,7 +640,6 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
         }
     }
     constexpr int JS = NVP + 1;   // Jacobian row stride in LDS
-    const int nr = N.nr;
     if (WANTJ) {
         // clear the Jacobian rows this lane owns (the row walk below adds into them) and its
         // species' entries of the T row (the reactions add into those; the T row's T entry is
@@ -646,50 +663,57 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
         iT = zbm::recip_from(T, __builtin_amdgcn_rcp(T));
     }
     double sT = 0.0, sTT = 0.0;
-    // the next reaction's parameters are loaded while the current one is processed
-    int4 nix = make_int4(0, -1, 0, 0);
-    double4 npr = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (c.gl < N.nr) {
-        nix = gload(N.rct + c.gl);
-        npr = gload(N.par + c.gl);
-    }
-    for (int r = c.gl; r < N.nr; r += L) {
-        const int4 ix = nix;
+    const int cs = nr + 1;   // column stride of the reaction columns
+    for (int rb = 0; rb < nr; rb += L) {
+        const int r = rb + c.gl;
+        const unsigned ab = nab;
         const double4 pr = npr;
-        if (r + L < N.nr) {
-            nix = gload(N.rct + r + L);
-            npr = gload(N.par + r + L);
+        if (rb + L < nr) {   // the next round's parameters while this one is processed
+            const int rn = r + L < nr ? r + L : nr - 1;
+            nab = gload(N.rct + rn);
+            npr = gload(N.par + rn);
         }
-        // sign-aware mass action: w = s k Ya Yb with s = -1 when both reactants are
-        // negative (k Ya |Ya| for A + A), so a negative abundance is pulled back to 0
-        const double ya = ybuf[ix.x];
-        const double yb0 = ix.y >= 0 ? ybuf[ix.y] : 1.0;
-        const double yb = (ya < 0.0 && yb0 < 0.0) ? -yb0 : yb0;
-        double k = rates_in_lds<NVP, L, LT>(c) ? ks[r] : 1.0;
-        if (N.thermal) k *= exp(pr.x + pr.y * lnT - pr.z * iT);
-        double kYb = k * yb;
-        double w = kYb * ya;
-        rx[r] = w;
-        if (WANTJ) {
-            double kb = ix.y >= 0 ? ((ya < 0.0 && yb0 < 0.0) ? -k * ya : k * ya) : 0.0;
-            double kt = N.thermal ? w * (pr.y + pr.z * iT) * iT : 0.0;
-            rx[nr + r] = kYb;
-            rx[2 * nr + r] = kb;
-            rx[3 * nr + r] = kt;
-            sTT += pr.w * kt;
+        if (r < nr) {
+            // sign-aware mass action: w = s k Ya Yb with s = -1 when both reactants are
+            // negative (k Ya |Ya| for A + A), so a negative abundance is pulled back to 0
+            const int oa = (int)(ab & 0xffffu), ob = (int)ab >> 16;
+            const double ya = *at(ybuf, oa);
+            const double yl = *at(ybuf, ob > 0 ? ob : 0);
+            const double yb0 = ob >= 0 ? yl : 1.0;
+            const bool neg = ya < 0.0 && yb0 < 0.0;
+            const double yb = neg ? -yb0 : yb0;
+            double k;
             if (N.thermal) {
-                // T row: q_r dw_r/dY for each reactant of the reaction, added in place, so
-                // that no lane walks a list of the reactions its species is consumed by
-                // (a chain of dependent table loads: 8 % of the burn on the 14-variable network)
-                JT *trow = jb + N.ns * JS;
-                __hip_atomic_fetch_add(trow + ix.x, (JT)(pr.w * kYb), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (ix.y >= 0)
-                    __hip_atomic_fetch_add(trow + ix.y, (JT)(pr.w * kb), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                k = exp(pr.x + pr.y * lnT - pr.z * iT);
+                if (rates_in_lds<NVP, L, LT>(c)) k *= ks[r];
+            } else {
+                k = ks[r];
             }
+            double kYb = k * yb;
+            double w = kYb * ya;
+            rx[r] = w;
+            if (WANTJ) {
+                double kb = ob >= 0 ? (neg ? -k * ya : k * ya) : 0.0;
+                double kt = N.thermal ? w * (pr.y + pr.z * iT) * iT : 0.0;
+                rx[cs + r] = kYb;
+                rx[2 * cs + r] = kb;
+                rx[3 * cs + r] = kt;
+                sTT += pr.w * kt;
+                if (N.thermal) {
+                    // T row: q_r dw_r/dY for each reactant of the reaction, added in place, so
+                    // that no lane walks a list of the reactions its species is consumed by
+                    // (a chain of dependent table loads: 8 % of the burn on the 14-variable network)
+                    JT *trow = jb + N.ns * JS;
+                    constexpr int sh = sizeof(JT) == 8 ? 0 : 1;
+                    __hip_atomic_fetch_add(at(trow, oa >> sh), (JT)(pr.w * kYb), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (ob >= 0)
+                        __hip_atomic_fetch_add(at(trow, ob >> sh), (JT)(pr.w * kb), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            sT += pr.w * w;
         }
-        sT += pr.w * w;
     }
     double fT = 0.0, JTT = 0.0;
     if (N.thermal) {
@@ -703,58 +727,51 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
         int i = row_of<NVP, L>(c, s);
         double fi = 0.0;
         if (i < N.ns) {
-            // two list entries per iteration (one 16-byte load), contributions added
-            // in list order; each entry carries the reactant columns it feeds
+            // four list entries a load, contributions added in list order; each entry carries
+            // the reactant columns it feeds.  A reaction of one reactant names it twice (its
+            // second derivative is 0), and padding adds 0.
             const int4 *lst = (const int4 *)(N.inv + i * N.inv_len);
             double jit = 0.0;
             JT *jrow = jb + i * JS;
-            auto jadd = [&](int y, double nu, double da, double db) {
-                const int a = y & 0xff, b = (y >> 8) - 1;
-                __hip_atomic_fetch_add(jrow + a, (JT)(nu * da), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (b >= 0)
-                    __hip_atomic_fetch_add(jrow + b, (JT)(nu * db), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-            };
-            // A pair of entries: the second is taken under a predicate (a padding entry
-            // reads slot 0 and adds nothing), so the LDS reads of both go out together.
-            auto pair = [&](int4 en) {
-                const int n0 = en.x >> 16, n1 = en.z >> 16;   // nu; 0 on a padding entry
-                const bool has1 = n1 != 0;
-                const int r0 = en.x & 0xffff, r1 = has1 ? (en.z & 0xffff) : 0;
-                const double nu0 = (double)n0;
-                const double nu1 = (double)n1;
-                const double w0 = rx[r0], w1 = rx[r1];
-                double p0 = 0.0, p1 = 0.0, q0 = 0.0, q1 = 0.0, t0 = 0.0, t1 = 0.0;
-                if (WANTJ) {
-                    p0 = rx[nr + r0]; p1 = rx[nr + r1];
-                    q0 = rx[2 * nr + r0]; q1 = rx[2 * nr + r1];
-                    t0 = rx[3 * nr + r0]; t1 = rx[3 * nr + r1];
-                }
-                fi = fma(nu0, w0, fi);
-                if (has1) fi = fma(nu1, w1, fi);
-                if (WANTJ) {
-                    jadd(en.y, nu0, p0, q0);
+            auto pair = [&](int e0, int e1) {
+                const int o0 = e0 & 0xffff, o1 = e1 & 0xffff;
+                const double nu0 = (double)(e0 >> 29), nu1 = (double)(e1 >> 29);
+                const double w0 = *at(rx, o0), w1 = *at(rx, o1);
+                if constexpr (!WANTJ) {
+                    fi = fma(nu0, w0, fi);
+                    fi = fma(nu1, w1, fi);
+                } else {
+                    const double p0 = *at(rx + cs, o0), p1 = *at(rx + cs, o1);
+                    const double q0 = *at(rx + 2 * cs, o0), q1 = *at(rx + 2 * cs, o1);
+                    const double t0 = *at(rx + 3 * cs, o0), t1 = *at(rx + 3 * cs, o1);
+                    fi = fma(nu0, w0, fi);
+                    fi = fma(nu1, w1, fi);
+                    auto jadd = [&](int e, double nu, double da, double db) {
+                        __hip_atomic_fetch_add(jrow + ((e >> 16) & 63), (JT)(nu * da), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(jrow + ((e >> 22) & 63), (JT)(nu * db), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    };
+                    jadd(e0, nu0, p0, q0);
                     jit = fma(nu0, t0, jit);
-                    if (has1) {
-                        jadd(en.w, nu1, p1, q1);
-                        jit = fma(nu1, t1, jit);
-                    }
+                    jadd(e1, nu1, p1, q1);
+                    jit = fma(nu1, t1, jit);
                 }
             };
             if (use_pre) {
-                // entries past the row's list are padding (nu = 0), skipped
-                sfor<0, (PMAX > 0 ? PMAX : 1)>([&](auto P) {
-                    if (P < n2 && (pre[P].x >> 16) != 0) pair(pre[P]);
+                sfor<0, (QMX > 0 ? QMX : 1)>([&](auto P) {
+                    if (P < n4) {
+                        pair(pre[P].x, pre[P].y);
+                        pair(pre[P].z, pre[P].w);
+                    }
                 });
             } else {
-                int4 nen = n2 > 0 ? gload(lst) : make_int4(0, 0, 0, 0);
-                for (int e = 0; e < n2; ++e) {
+                int4 nen = gload(lst);
+                for (int e = 0; e < n4; ++e) {
                     const int4 en = nen;
-                    if (e + 1 < n2) nen = gload(lst + e + 1);
-                    if ((en.x >> 16) == 0) break;
-                    pair(en);
-                    if ((en.z >> 16) == 0) break;
+                    if (e + 1 < n4) nen = gload(lst + e + 1);
+                    pair(en.x, en.y);
+                    pair(en.z, en.w);
                 }
             }
             if (WANTJ && N.thermal) jrow[N.ns] = (JT)jit;
@@ -1833,6 +1850,10 @@ __device__ __forceinline__ int zone_start(const Ctx &c, Zone<NVP, L, LT> &z)
     const double *row = SG.state + c.zone * (N.ns + 1);
     const double *scale = SG.scale, *source = SG.source;
     double *ks = c.S + c.lay.ks;
+    if (c.gl == 0) {   // the slot that padding entries of the row lists read, in every column
+        double *rx = c.S + c.lay.rx;
+        for (int k = 0; k < 4; ++k) rx[k * (N.nr + 1) + N.nr] = 0.0;
+    }
     if (rates_in_lds<NVP, L, LT>(c)) {
         for (int r = c.gl; r < N.nr; r += L) {
             double s = scale ? scale[c.zone * N.nr + r] : 1.0;
@@ -2388,19 +2409,15 @@ __device__ __forceinline__ int zone_attempt_rkc(const Ctx &c, Zone<NVP, L, LT> &
     return RUNNING;
 }
 
-// The zone's counters, plus those of its first run while it is retried (in LDS) and, in the
-// FP64 run of the fallback, those its mixed-precision run left in the stats row.
+// The zone's counters, plus those that an earlier run of it left in the stats row (its first run
+// while it is retried, the mixed-precision run in the FP64 run of the fallback).
 template <int NVP, int L, class LT>
 __device__ __forceinline__ void write_stats(const Ctx &c, const Zone<NVP, L, LT> &z, bool add_row)
 {
     int32_t *o = seg_of(c).stats + c.zone * 7;
     int add[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (z.tries > 0) {
-        const int *cnt = (const int *)(c.S + c.lay.cnt);
-        for (int k = 0; k < 7; ++k) add[k] = cnt[k];
-    }
     if (add_row)
-        for (int k = 0; k < 7; ++k) add[k] += o[k];
+        for (int k = 0; k < 7; ++k) add[k] = o[k];
     o[0] = z.nst + add[0]; o[1] = z.nfe + add[1]; o[2] = z.nje + add[2]; o[3] = z.nlu + add[3];
     o[4] = z.nni + add[4]; o[5] = z.netf + add[5]; o[6] = z.ncf + add[6];
 }
@@ -2420,7 +2437,7 @@ __device__ __forceinline__ bool zone_defer(const Ctx &c, const Zone<NVP, L, LT> 
     if (idx >= (unsigned long long)FB_CAP) return false;
     if (c.gl == 0) {
         A.fb[MAXSEG + seg * FB_CAP + idx] = (unsigned long long)c.zone;
-        if (seg_of(c).stats) write_stats(c, z, false);
+        if (seg_of(c).stats) write_stats(c, z, z.tries > 0);
     }
     return true;
 }
@@ -2443,7 +2460,7 @@ __device__ __forceinline__ void zone_finish(const Ctx &c, Zone<NVP, L, LT> &z, i
     if (c.gl == 0) {
         int32_t *st = seg_of(c).status;
         if (st) st[c.zone] = status;
-        if (seg_of(c).stats) write_stats(c, z, replay);
+        if (seg_of(c).stats) write_stats(c, z, replay || z.tries > 0);
         if (status != ZB_ZONE_OK && status != ZB_ZONE_OK_RETRY && status != ZB_ZONE_OK_FP64)
             atomicAdd(A.nfail, 1ull);
     }
@@ -2582,12 +2599,8 @@ void burn_kernel(BurnArgs A)
                 if (st != ZB_ZONE_OK && A.retry && z.tries == 0) {
                     // Zone-by-zone retry with the retry tolerances, from the zone's input
                     // (still in memory: results are written only when a zone ends).  The
-                    // first run's counters wait in LDS and are added at the end.
-                    if (c.gl == 0) {
-                        int *cnt = (int *)(c.S + c.lay.cnt);
-                        cnt[0] = z.nst; cnt[1] = z.nfe; cnt[2] = z.nje; cnt[3] = z.nlu;
-                        cnt[4] = z.nni; cnt[5] = z.netf; cnt[6] = z.ncf;
-                    }
+                    // first run's counters wait in the stats row and are added at the end.
+                    if (c.gl == 0 && seg_of(c).stats) write_stats(c, z, A.fb_mode == 2);
                     z.rtol = A.retry_rtol;
                     z.atol = A.retry_atol;
                     z.max_steps = A.retry_max_steps;

@@ -140,6 +140,7 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     if (nr > 0 && (!d->reactant || !d->product || !d->lnA || !d->n_exp || !d->E || (th && !d->q)))
         return fail(ZB_EINVAL, "NULL reaction array");
     std::vector<int4> rct(std::max(nr, 1));
+    std::vector<unsigned> rab(std::max(nr, 1), 0u);   // packed as DevNet::rct
     std::vector<double4> par(std::max(nr, 1));
     for (int r = 0; r < nr; ++r) {
         int a = d->reactant[2 * r], b = d->reactant[2 * r + 1];
@@ -150,25 +151,28 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
         if (!isfinite(d->lnA[r]) || !isfinite(d->n_exp[r]) || !isfinite(d->E[r]) || !isfinite(q))
             return fail(ZB_EINVAL, "reaction %d: non-finite parameter", r);
         rct[r] = make_int4(a, b, c, e);
+        rab[r] = (unsigned)(8 * a) | ((unsigned)(8 * b) << 16);
         par[r] = make_double4(d->lnA[r], d->n_exp[r], d->E[r], q);
     }
     // per-species involvement lists (net stoichiometry != 0)
-    std::vector<std::vector<int2>> inv(ns);
+    std::vector<std::vector<unsigned>> inv(ns);
     for (int r = 0; r < nr; ++r) {
         const int4 x = rct[r];
+        const unsigned cols = (unsigned)x.x << 16 | (unsigned)(x.y >= 0 ? x.y : x.x) << 22;
         for (int i = 0; i < ns; ++i) {
             int nu = (x.z == i) + (x.w == i) - (x.x == i) - (x.y == i);
-            if (nu != 0) inv[i].push_back(make_int2(r | (int)((unsigned)nu << 16), x.x | ((x.y + 1) << 8)));
+            if (nu != 0) inv[i].push_back((unsigned)(8 * r) | cols | ((unsigned)nu << 29));
         }
     }
-    int inv_len = 2;
+    int inv_len = 4;
     for (int i = 0; i < ns; ++i) inv_len = std::max<int>(inv_len, (int)inv[i].size());
-    inv_len += inv_len & 1;   // even: the kernels take two entries per iteration
-    std::vector<int2> invf((size_t)ns * inv_len, make_int2(0, 0));   // nu = 0 pads a row
+    inv_len = (inv_len + 3) & ~3;   // the kernels take four entries per load
+    std::vector<unsigned> invf((size_t)ns * inv_len, (unsigned)(8 * nr));   // padding: the 0 slot
     for (int i = 0; i < ns; ++i) std::copy(inv[i].begin(), inv[i].end(), invf.begin() + (size_t)i * inv_len);
-    size_t o_rct = 0, o_par = o_rct + sizeof(int4) * rct.size();
-    size_t o_inv = o_par + sizeof(double4) * par.size();
-    size_t bytes = o_inv + sizeof(int2) * invf.size();
+    // the parameters first: each table then starts on its own alignment (32, 16, 4 bytes)
+    size_t o_par = 0, o_inv = o_par + sizeof(double4) * par.size();
+    size_t o_rct = o_inv + sizeof(unsigned) * invf.size();
+    size_t bytes = o_rct + sizeof(unsigned) * rab.size();
     zb_network *n = new (std::nothrow) zb_network();
     if (!n) return fail(ZB_ENOMEM, "host allocation failed");
     DeviceGuard g(ctx->device);
@@ -178,9 +182,9 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
         return fail(ZB_ENOMEM, "device allocation of %zu bytes failed", bytes);
     }
     std::vector<char> host(bytes);
-    memcpy(host.data() + o_rct, rct.data(), sizeof(int4) * rct.size());
+    memcpy(host.data() + o_rct, rab.data(), sizeof(unsigned) * rab.size());
     memcpy(host.data() + o_par, par.data(), sizeof(double4) * par.size());
-    memcpy(host.data() + o_inv, invf.data(), sizeof(int2) * invf.size());
+    memcpy(host.data() + o_inv, invf.data(), sizeof(unsigned) * invf.size());
     if (hipMemcpy(dm, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(dm);
         delete n;
@@ -193,9 +197,9 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     n->dn.thermal = th;
     n->dn.nr = nr;
     n->dn.inv_len = inv_len;
-    n->dn.rct = (const int4 *)(dm + o_rct);
+    n->dn.rct = (const unsigned *)(dm + o_rct);
     n->dn.par = (const double4 *)(dm + o_par);
-    n->dn.inv = (const int2 *)(dm + o_inv);
+    n->dn.inv = (const unsigned *)(dm + o_inv);
     *out = n;
     return ZB_OK;
 }

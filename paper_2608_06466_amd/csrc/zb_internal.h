@@ -11,20 +11,22 @@ constexpr int NVMAX = 64;    // largest number of integrated variables
 constexpr int RMAX = 4096;   // largest number of reactions
 
 // A network as the kernels read it.  Built once per network by the host.
-//  rct[r] = (a, b, c, d): reactants a, b and products c, d (-1 when absent).
+//  rct[r] = 8 a | 8 b << 16: byte offsets of the reactants in an array of doubles (b a signed
+//              field, -1 when absent).
 //  par[r] = (lnA, n, E, q).
 //  inv[i][e], for every reaction r whose net stoichiometry nu_ir in species i is
-//              non-zero: .x = r | nu_ir << 16 (nu_ir a signed 16-bit field, read with
-//              an arithmetic shift), .y = a_r | (b_r + 1) << 8 (the reactant columns
-//              the row's Jacobian entries go to, so no second lookup is needed);
-//              entries with nu = 0 (.x = 0) pad the row.
-//  The row length inv_len is even (the kernels read two entries at a time).
+//              non-zero, in one word: 8 r (16 bits, the reaction's place in a column of
+//              doubles), a_r and b_r (6 bits each, the Jacobian columns the row's entries go
+//              to; a_r again when the reaction has one reactant), nu_ir (3 bits, signed; read
+//              with an arithmetic shift).  Rows are padded with r = nr, nu = 0, the slot past
+//              the reactions, which holds 0 in every column.
+//  The row length inv_len is a multiple of 4 (the kernels read four entries at a time).
 struct DevNet {
     int ns, nv, thermal, nr;
     int inv_len;
-    const int4 *rct;
+    const unsigned *rct;
     const double4 *par;
-    const int2 *inv;
+    const unsigned *inv;
 };
 
 // One run of zones that share a network and tolerances.
@@ -98,7 +100,7 @@ __host__ __device__ constexpr bool hist_regs(int nvp, int L, bool mixed, int met
 
 // Per-group LDS layout (in doubles).  Everything a zone group exchanges lives here.
 struct LdsLayout {
-    int cnt, zs, ybuf, wbuf, prow, ks, rx, jbuf, vc, total;
+    int zs, ybuf, wbuf, prow, ks, rx, jbuf, vc, total;
 };
 
 // Variable-coefficient BDF slots (kernels of that form only): the accepted step sizes,
@@ -133,14 +135,13 @@ __host__ __device__ inline LdsLayout lds_layout(int nvp, int L, int rpl, int nr,
     const bool trim = lds_trim(L, rpl, jf32);
     LdsLayout o;
     int p = 0;
-    o.cnt = p;  p += 4;               // counters of a zone's first run while it is retried
     o.zs = p;   p += hregs ? 0 : (QMAX + 1) * (trim ? nvp : L * rpl);
     o.ybuf = p; p += nvp;
     o.wbuf = p; p += nvp;
     o.prow = p; p += trim ? 0 : nvp;
     o.ks = p;   p += (trim && !rates) ? 0 : nr;
     p = (p + 1) & ~1;
-    o.rx = p;   p += 4 * nr;          // w, dw/dYa, dw/dYb, dw/dT: four columns of nr
+    o.rx = p;   p += 4 * (nr + 1);    // w, dw/dYa, dw/dYb, dw/dT: four columns of nr and a 0
     o.jbuf = p;                       // Jacobian rows with an odd stride (no bank conflicts)
     p += jf32 ? (nvp * (nvp + 1) + 1) / 2 : nvp * (nvp + 1);
     o.vc = p;   p += vc ? VC_SLOTS : 0;

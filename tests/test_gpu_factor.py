@@ -49,3 +49,51 @@ def test_linear_networks_at_the_edges(zbm, ns, precision):
         for z in range(len(st)):
             assert gated(out[z, :ns], ref[z], 1e-8, 1e-12) < 1e-6, (policy, z)
     net.close()
+
+
+def _mixed_orders(ns, seed):
+    """Thermal network of one- and two-reactant reactions: every third reaction of a random
+    network loses its second reactant and product, every seventh consumes one species twice, every
+    fifth has its first reactant among the products."""
+    net = W.random_network(ns, 3 * ns, seed, E_range=(1.0e3, 2.0e4))
+    ra, pa = net["reactant"], net["product"]
+    pa[::5, 0] = ra[::5, 0]
+    ra[::7, 1] = ra[::7, 0]
+    ra[::3, 1] = pa[::3, 1] = -1
+    pa[::3, 0] = (ra[::3, 0] + 1) % ns
+    net["lnA"] = net["lnA"] * 0.7
+    net["q"] = net["q"] * 1e-3   # the cycles among them would heat without end
+    return net
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("ns", [3, 7, 13, 15, 21, 31, 33, 47])
+def test_reaction_tables(zbm, ns, precision):
+    """The packed reaction and row tables of the evaluation: unary, A + A and catalytic reactions
+    on every kernel size, against the oracle's bars at rtol 1e-8."""
+    zb, ctx = zbm
+    net_d = _mixed_orders(ns, 70 + ns)
+    st = W.random_zones(net_d, 21, 71 + ns, T_range=(300.0, 1500.0), T_dist="loguniform")
+    net = zb.Network(ctx, net_d)
+    t = torch.tensor(st, device="cuda:0")
+    status, stats = zb.burn(ctx, net, t, 1.0, 1e-8, 1e-12, precision=precision)
+    assert zb.sync(ctx) == 0
+    check(f"tables nv {ns + 1} {precision}", (t.cpu().numpy(), status.cpu().numpy(), stats.cpu().numpy()),
+          oracle.burn(net_d, st, 1.0, 1e-8, 1e-12), 1e-8, 1e-12, ns + 1,
+          fine=oracle.burn(net_d, st, 1.0, 1e-10, 1e-14, max_steps=10000000), state_in=st)
+    net.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("ns", [4, 13, 48])
+def test_no_reactions(zbm, ns, precision):
+    """No reactions (padding entries only): every zone ends as it began."""
+    zb, ctx = zbm
+    net_d = W.random_network(ns, 0, 5, thermal=ns < 48)
+    st = W.random_zones(net_d, 5, 6)
+    net = zb.Network(ctx, net_d)
+    t = torch.tensor(st, device="cuda:0")
+    zb.burn(ctx, net, t, 1.0, 1e-8, 1e-12, precision=precision)
+    assert zb.sync(ctx) == 0
+    assert np.array_equal(t.cpu().numpy(), st)
+    net.close()
