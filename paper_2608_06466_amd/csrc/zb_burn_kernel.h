@@ -543,6 +543,9 @@ __device__ __forceinline__ DevNet net_of(const Ctx &c)
     r.rct = n.rct;
     r.par = n.par;
     r.inv = n.inv;
+    r.con_len = n.con_len;
+    r.con = n.con;
+    r.conq = n.conq;
     return r;
 }
 
@@ -649,7 +652,7 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
             int i = row_of<NVP, L>(c, S);
             if (i < N.ns) {
                 sfor<0, NVP>([&](auto J) { jb[i * JS + J] = JT(0); });
-                if (N.thermal) jb[N.ns * JS + i] = JT(0);
+                if (sizeof(JT) == 8 && N.thermal) jb[N.ns * JS + i] = JT(0);
             }
         });
     }
@@ -699,16 +702,15 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
                 rx[2 * cs + r] = kb;
                 rx[3 * cs + r] = kt;
                 sTT += pr.w * kt;
-                if (N.thermal) {
+                if (sizeof(JT) == 8 && N.thermal) {
                     // T row: q_r dw_r/dY for each reactant of the reaction, added in place, so
                     // that no lane walks a list of the reactions its species is consumed by
                     // (a chain of dependent table loads: 8 % of the burn on the 14-variable network)
                     JT *trow = jb + N.ns * JS;
-                    constexpr int sh = sizeof(JT) == 8 ? 0 : 1;
-                    __hip_atomic_fetch_add(at(trow, oa >> sh), (JT)(pr.w * kYb), __ATOMIC_RELAXED,
+                    __hip_atomic_fetch_add(at(trow, oa), (JT)(pr.w * kYb), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (ob >= 0)
-                        __hip_atomic_fetch_add(at(trow, ob >> sh), (JT)(pr.w * kb), __ATOMIC_RELAXED,
+                        __hip_atomic_fetch_add(at(trow, ob), (JT)(pr.w * kb), __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
@@ -747,6 +749,18 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
                     fi = fma(nu0, w0, fi);
                     fi = fma(nu1, w1, fi);
                     auto jadd = [&](int e, double nu, double da, double db) {
+                        if constexpr (sizeof(JT) == 4) {
+                            // FP32 rows: read, add, write.  The row is this lane's alone, and
+                            // ds_add_f32 takes 3 cycles a lane (194 an instruction a CU, against
+                            // 9 to 20 for ds_add_f64 and 21 for the read and write)
+                            const int a = (e >> 16) & 63, b = (e >> 22) & 63;
+                            float xa = jrow[a], xb = jrow[b];
+                            xa += (float)(nu * da);
+                            xb = (a == b ? xa : xb) + (float)(nu * db);
+                            jrow[a] = xa;
+                            jrow[b] = xb;
+                            return;
+                        }
                         __hip_atomic_fetch_add(jrow + ((e >> 16) & 63), (JT)(nu * da), __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_WORKGROUP);
                         __hip_atomic_fetch_add(jrow + ((e >> 22) & 63), (JT)(nu * db), __ATOMIC_RELAXED,
@@ -775,6 +789,33 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
                 }
             }
             if (WANTJ && N.thermal) jrow[N.ns] = (JT)jit;
+            if constexpr (WANTJ && sizeof(JT) == 4) {
+                // FP32 T row: the species' lane sums q_r dw_r/dY_i over the reactions it is a
+                // reactant of, in the order the reactions' lanes would add them (ds_add_f32 is
+                // too slow, above)
+                if (N.thermal) {
+                    const int m4 = N.con_len / 4;
+                    const int4 *cl = (const int4 *)(N.con + i * N.con_len);
+                    const double4 *ql = (const double4 *)(N.conq + i * N.con_len);
+                    int4 ne = gload(cl);
+                    double4 nq = gload(ql);
+                    float t = 0.0f;
+                    for (int e = 0; e < m4; ++e) {
+                        const int4 en = ne;
+                        const double4 q = nq;
+                        if (e + 1 < m4) {
+                            ne = gload(cl + e + 1);
+                            nq = gload(ql + e + 1);
+                        }
+                        const double v0 = *at(rx, en.x), v1 = *at(rx, en.y), v2 = *at(rx, en.z), v3 = *at(rx, en.w);
+                        t += (float)(q.x * v0);
+                        t += (float)(q.y * v1);
+                        t += (float)(q.z * v2);
+                        t += (float)(q.w * v3);
+                    }
+                    jb[N.ns * JS + i] = t;
+                }
+            }
         } else if (N.thermal && i == N.ns) {
             fi = fT;
             if (WANTJ) jb[N.ns * JS + N.ns] = (JT)JTT;

@@ -169,9 +169,29 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     inv_len = (inv_len + 3) & ~3;   // the kernels take four entries per load
     std::vector<unsigned> invf((size_t)ns * inv_len, (unsigned)(8 * nr));   // padding: the 0 slot
     for (int i = 0; i < ns; ++i) std::copy(inv[i].begin(), inv[i].end(), invf.begin() + (size_t)i * inv_len);
+    // the reactions each species is a reactant of (DevNet::con)
+    std::vector<std::vector<std::pair<unsigned, double>>> con(ns);
+    for (int r0 = 0; r0 < nr; r0 += 64)
+        for (int side = 0; side < 2; ++side)
+            for (int r = r0; r < std::min(nr, r0 + 64); ++r) {
+                const int i = side ? rct[r].y : rct[r].x;
+                if (i >= 0) con[i].push_back({(unsigned)(8 * ((side + 1) * (nr + 1) + r)), par[r].w});
+            }
+    int con_len = 4;
+    for (int i = 0; i < ns; ++i) con_len = std::max<int>(con_len, (int)con[i].size());
+    con_len = (con_len + 3) & ~3;
+    std::vector<unsigned> conf((size_t)ns * con_len, (unsigned)(8 * nr));
+    std::vector<double> conq((size_t)ns * con_len, 0.0);
+    for (int i = 0; i < ns; ++i)
+        for (size_t e = 0; e < con[i].size(); ++e) {
+            conf[(size_t)i * con_len + e] = con[i][e].first;
+            conq[(size_t)i * con_len + e] = con[i][e].second;
+        }
     // the parameters first: each table then starts on its own alignment (32, 16, 4 bytes)
-    size_t o_par = 0, o_inv = o_par + sizeof(double4) * par.size();
-    size_t o_rct = o_inv + sizeof(unsigned) * invf.size();
+    size_t o_par = 0, o_conq = o_par + sizeof(double4) * par.size();
+    size_t o_inv = o_conq + sizeof(double) * conq.size();
+    size_t o_con = o_inv + sizeof(unsigned) * invf.size();
+    size_t o_rct = o_con + sizeof(unsigned) * conf.size();
     size_t bytes = o_rct + sizeof(unsigned) * rab.size();
     zb_network *n = new (std::nothrow) zb_network();
     if (!n) return fail(ZB_ENOMEM, "host allocation failed");
@@ -184,6 +204,8 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     std::vector<char> host(bytes);
     memcpy(host.data() + o_rct, rab.data(), sizeof(unsigned) * rab.size());
     memcpy(host.data() + o_par, par.data(), sizeof(double4) * par.size());
+    memcpy(host.data() + o_conq, conq.data(), sizeof(double) * conq.size());
+    memcpy(host.data() + o_con, conf.data(), sizeof(unsigned) * conf.size());
     memcpy(host.data() + o_inv, invf.data(), sizeof(unsigned) * invf.size());
     if (hipMemcpy(dm, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(dm);
@@ -200,6 +222,9 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     n->dn.rct = (const unsigned *)(dm + o_rct);
     n->dn.par = (const double4 *)(dm + o_par);
     n->dn.inv = (const unsigned *)(dm + o_inv);
+    n->dn.con_len = con_len;
+    n->dn.con = (const unsigned *)(dm + o_con);
+    n->dn.conq = (const double *)(dm + o_conq);
     *out = n;
     return ZB_OK;
 }

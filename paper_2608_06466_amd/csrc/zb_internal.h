@@ -21,12 +21,20 @@ constexpr int RMAX = 4096;   // largest number of reactions
 //              with an arithmetic shift).  Rows are padded with r = nr, nu = 0, the slot past
 //              the reactions, which holds 0 in every column.
 //  The row length inv_len is a multiple of 4 (the kernels read four entries at a time).
+//  con[i][e], for every reaction that species i is a reactant of: the byte offset of dw_r/dY_i
+//              in the reaction columns (8 (nr + 1 + r) for reactant a, 8 (2 (nr + 1) + r)
+//              for b), conq[i][e] the reaction's q; rows padded with the 0 slot and q = 0 to
+//              con_len, a multiple of 4.  In the order in which 64 lanes that take the
+//              reactions in turn, a before b, come to the species.
 struct DevNet {
     int ns, nv, thermal, nr;
     int inv_len;
     const unsigned *rct;
     const double4 *par;
     const unsigned *inv;
+    int con_len;
+    const unsigned *con;
+    const double *conq;
 };
 
 // One run of zones that share a network and tolerances.
