@@ -1119,7 +1119,7 @@ __device__ __forceinline__ void off_steps(LT &v, const LT *m, LT t)
 // solve, which reads a step's value with one v_readlane (nv 48, 16384 zones mixed: 372 ms so, 380
 // in blocks; FP64, two v_readlane a value, 8192 zones: 271 ms so, 259 in blocks).
 template <int L, class LT>
-constexpr bool dpp_solve() { return L >= 16 && !(L == 64 && sizeof(LT) == 4); }
+constexpr bool dpp_solve() { return L >= 16; }
 
 // L U x = v with the factors' row i in lane i (M_ii = 0, d = 1 / U_ii): v comes back as U_ii x_i,
 // every sum taken in the order of the plain loops.  The blocks of 16 rows in turn: the steps
