@@ -653,6 +653,8 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
             if (i < N.ns) {
                 sfor<0, NVP>([&](auto J) { jb[i * JS + J] = JT(0); });
                 if (sizeof(JT) == 8 && N.thermal) jb[N.ns * JS + i] = JT(0);
+            } else if (i < N.nv) {
+                for (int J = N.nv; J < NVP; ++J) jb[i * JS + J] = JT(0);
             }
         });
     }
@@ -841,6 +843,11 @@ __device__ __forceinline__ void fd_jacobian(const Ctx &c, Zone<NVP, L, LT> &z,
     JT *jb = (JT *)(c.S + c.lay.jbuf);
     eval<false>(c, z, yv, fo);
     const int nv = c.nv;
+    sfor<0, RPL>([&](auto S) {
+        const int i = row_of<NVP, L>(c, S);
+        for (int J = nv; J < NVP; ++J)
+            if (i < nv) jb[i * JS + J] = JT(0);
+    });
     for (int j = 0; j < nv; ++j) {
         double yp[RPL], fp[RPL];
         double dj = 0.0;
@@ -877,7 +884,10 @@ __device__ __forceinline__ void fd_jacobian(const Ctx &c, Zone<NVP, L, LT> &z,
 template <int NVP, int L, class LT>
 constexpr bool kept_order() { return Zone<NVP, L, LT>::RPL == 1 && L >= 2; }
 
-template <int NVP, int L, class LT>
+// FORM: M_KEPT and M_AGAIN where an order is kept (M_AGAIN after that order was refused), else
+// M_PLAIN.
+enum { M_PLAIN, M_KEPT, M_AGAIN };
+template <int FORM, int NVP, int L, class LT>
 __device__ __forceinline__ void form_M(const Ctx &c, Zone<NVP, L, LT> &z, double gamma)
 {
     constexpr int RPL = Zone<NVP, L, LT>::RPL;
@@ -895,8 +905,25 @@ __device__ __forceinline__ void form_M(const Ctx &c, Zone<NVP, L, LT> &z, double
         double mrow[NVP];
         if (i < N.nv) {
             sfor<0, NVP>([&](auto J) {
-                double m = (J == i ? 1.0 : 0.0) - gamma * (double)jb[i * JS + J];
-                if (J >= N.nv) m = (J == i) ? 1.0 : 0.0;
+                double m;
+                if constexpr (FORM == M_PLAIN) {
+                    m = (J == i ? 1.0 : 0.0) - gamma * (double)jb[i * JS + J];
+                    if (J >= N.nv) m = (J == i) ? 1.0 : 0.0;
+                } else {
+                    // Columns past nv hold 0 (eval, fd_jacobian), so no select on nv follows (a
+                    // fifth of the instructions here).  Products are rounded, but for the first
+                    // column's after a refused order, which is fused: the compiler's choices with
+                    // the select, kept so that results stay the same bits.
+#pragma clang fp contract(off)
+                    const double m0 = (J == i) ? 1.0 : 0.0;
+                    const double jij = (double)jb[i * JS + J];
+                    if constexpr (FORM == M_AGAIN && J == 0) {
+                        m = fma(-gamma, jij, m0);
+                    } else {
+                        const double x = gamma * jij;
+                        m = m0 - x;
+                    }
+                }
                 if (MIXED) {
                     m *= wb[J];
                     rmax = fmax(rmax, fabs(m));
@@ -1115,10 +1142,9 @@ __device__ __forceinline__ void off_steps(LT &v, const LT *m, LT t)
 #undef ZB_EXEC_BACK
 #undef ZB_EXEC_SAVE
 
-// Where tri_solve runs: one row a lane in groups of 16 lanes or more, but for the whole-wave FP32
-// solve, which reads a step's value with one v_readlane (nv 48, 16384 zones mixed: 372 ms so, 380
-// in blocks; FP64, two v_readlane a value, 8192 zones: 271 ms so, 259 in blocks).
-template <int L, class LT>
+// Where tri_solve runs: one row a lane in groups of 16 lanes or more (smaller groups share a DPP row,
+// whose broadcast would cross them).
+template <int L>
 constexpr bool dpp_solve() { return L >= 16; }
 
 // L U x = v with the factors' row i in lane i (M_ii = 0, d = 1 / U_ii): v comes back as U_ii x_i,
@@ -1499,51 +1525,53 @@ __device__ __forceinline__ bool lane_in(unsigned long long m)
 // instruction reads what another wrote (own: p is d, each lane's column read before it is
 // written).  14 variables with it in the LU: FP64 (50021 zones) 135.0 -> 132.1 ms, mixed (2^18)
 // 549 -> 539 ms.
+// The columns are NX of one array (xd, xp) and then NY of another (yd, yp), elements B to E - 1 of
+// both together here, eight a block (a block's wait states cost as much as a column).
 #define ZB_UPD(T, j) "v_fmac_" T "_dpp %[d" #j "], %[p" #j "], -%[l] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n"
 #define ZB_UPS(T, j) "v_fmac_" T "_dpp %[d" #j "], %[d" #j "], -%[l] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n"
-#define ZB_D(j) [d##j] "+v"(d[j])
-#define ZB_P(j) [p##j] "v"(p[j])
+#define ZB_D(j) [d##j] "+v"(B + j < NX ? xd[B + j] : yd[B + j - NX])
+#define ZB_P(j) [p##j] "v"(B + j < NX ? xp[B + j] : yp[B + j - NX])
+#define ZB_8(M) M(0), M(1), M(2), M(3), M(4), M(5), M(6), M(7)
+#define ZB_4(M) M(0), M(1), M(2), M(3)
+#define ZB_S8(M, T) M(T, 0) M(T, 1) M(T, 2) M(T, 3) M(T, 4) M(T, 5) M(T, 6) M(T, 7)
+#define ZB_S4(M, T) M(T, 0) M(T, 1) M(T, 2) M(T, 3)
 #define ZB_UPDATE(T)                                                                                       \
-    if constexpr (N == 4 && OWN)                                                                           \
-        asm("s_nop 1\n" ZB_UPS(T, 0) ZB_UPS(T, 1) ZB_UPS(T, 2) ZB_UPS(T, 3)                               \
-            : ZB_D(0), ZB_D(1), ZB_D(2), ZB_D(3) : [l] "v"(l), [k] "i"(K % 16));                           \
+    if constexpr (N == 8 && OWN)                                                                           \
+        asm("s_nop 1\n" ZB_S8(ZB_UPS, T) : ZB_8(ZB_D) : [l] "v"(l), [k] "i"(K % 16));                     \
+    else if constexpr (N == 4 && OWN)                                                                      \
+        asm("s_nop 1\n" ZB_S4(ZB_UPS, T) : ZB_4(ZB_D) : [l] "v"(l), [k] "i"(K % 16));                     \
     else if constexpr (N == 2 && OWN)                                                                      \
         asm("s_nop 1\n" ZB_UPS(T, 0) ZB_UPS(T, 1) : ZB_D(0), ZB_D(1) : [l] "v"(l), [k] "i"(K % 16));      \
     else if constexpr (OWN)                                                                                \
         asm("s_nop 1\n" ZB_UPS(T, 0) : ZB_D(0) : [l] "v"(l), [k] "i"(K % 16));                            \
+    else if constexpr (N == 8)                                                                             \
+        asm("s_nop 1\n" ZB_S8(ZB_UPD, T) : ZB_8(ZB_D) : ZB_8(ZB_P), [l] "v"(l), [k] "i"(K % 16));         \
     else if constexpr (N == 4)                                                                             \
-        asm("s_nop 1\n" ZB_UPD(T, 0) ZB_UPD(T, 1) ZB_UPD(T, 2) ZB_UPD(T, 3)                               \
-            : ZB_D(0), ZB_D(1), ZB_D(2), ZB_D(3)                                                           \
-            : ZB_P(0), ZB_P(1), ZB_P(2), ZB_P(3), [l] "v"(l), [k] "i"(K % 16));                            \
+        asm("s_nop 1\n" ZB_S4(ZB_UPD, T) : ZB_4(ZB_D) : ZB_4(ZB_P), [l] "v"(l), [k] "i"(K % 16));         \
     else if constexpr (N == 2)                                                                             \
         asm("s_nop 1\n" ZB_UPD(T, 0) ZB_UPD(T, 1)                                                         \
             : ZB_D(0), ZB_D(1) : ZB_P(0), ZB_P(1), [l] "v"(l), [k] "i"(K % 16));                           \
     else                                                                                                   \
         asm("s_nop 1\n" ZB_UPD(T, 0) : ZB_D(0) : ZB_P(0), [l] "v"(l), [k] "i"(K % 16));
-template <int K, int N, bool OWN, class LT>
-__device__ __forceinline__ void row_update_n(LT *d, const LT *p, LT l)
+template <int K, bool OWN, int NX, int NY, int MAXN = 8, int B = 0, class LT>
+__device__ __forceinline__ void row_update(LT *xd, const LT *xp, LT *yd, const LT *yp, LT l)
 {
-    if constexpr (sizeof(LT) == 4) { ZB_UPDATE("f32") } else { ZB_UPDATE("f64") }
+    constexpr int left = NX + NY - B;
+    constexpr int N = left >= 8 && MAXN == 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : left;
+    if constexpr (N > 0) {
+        if constexpr (sizeof(LT) == 4) { ZB_UPDATE("f32") } else { ZB_UPDATE("f64") }
+        row_update<K, OWN, NX, NY, MAXN, B + N>(xd, xp, yd, yp, l);
+    }
 }
 #undef ZB_UPDATE
+#undef ZB_S4
+#undef ZB_S8
+#undef ZB_4
+#undef ZB_8
 #undef ZB_P
 #undef ZB_D
 #undef ZB_UPS
 #undef ZB_UPD
-
-template <int K, int B, int E, bool OWN, class LT>
-__device__ __forceinline__ void row_update(LT *d, const LT *p, LT l)
-{
-    if constexpr (E - B >= 4) {
-        row_update_n<K, 4, OWN>(d + B, p + B, l);
-        row_update<K, B + 4, E, OWN>(d, p, l);
-    } else if constexpr (E - B >= 2) {
-        row_update_n<K, 2, OWN>(d + B, p + B, l);
-        row_update<K, B + 2, E, OWN>(d, p, l);
-    } else if constexpr (E - B == 1) {
-        row_update_n<K, 1, OWN>(d + B, p + B, l);
-    }
-}
 
 // 4 x 4 (L = 64) or 2 x 2 (L = 32) transpose of registers against the group's 16-lane rows: x[c]
 // of lane row s becomes x[s] of lane row c.  Its own inverse.
@@ -1597,6 +1625,11 @@ __device__ __forceinline__ bool lu_kept_spread(const Ctx &c, Zone<NVP, L, LT> &z
 {
     constexpr int C = L / 16, NJ = NVP / C, S = (NVP + 15) / 16;
     static_assert(NVP % C == 0 && S <= C, "columns in whole sets");
+    // A panel's columns go back to their lane rows one by one in the whole-wave FP64 kernel, whose
+    // registers they would fill (48 variables, 8192 zones: 223 ms with them kept to the panel's
+    // end, 212 so), all at the end elsewhere (48 variables mixed, 16384 zones: 268 ms, 356 one by
+    // one; 22 variables FP64, 20011 zones: 87 and 91 ms)
+    constexpr bool BACK_EACH = L == 64 && sizeof(LT) == 8;
     const int nv = own_copy(c.nv);
     LT Y[S][NJ];
     sfor<0, NJ>([&](auto J) {
@@ -1642,21 +1675,28 @@ __device__ __forceinline__ bool lu_kept_spread(const Ctx &c, Zone<NVP, L, LT> &z
                 } else {
                     X[r][q] = l;
                 }
-                // rows below first: they read the pivot's block before its own update
+                // the finished column back to the lane row that keeps it
+                if constexpr (BACK_EACH) Y[r][p] = lane_in(lanes_in<L>(16 * q, 16 * q + 15)) ? X[r][q] : Y[r][p];
             });
+            // the rows of the pivot's block last: the others read them
             sfor<0, S - sk>([&](auto RR) {
                 constexpr int r = S - 1 - RR;
                 LT l = X[r][q];
                 if constexpr (r == sk) l = gt ? l : LT(0);
-                row_update<k, q + 1, C, (r == sk)>(X[r], X[sk], l);
-                row_update<k, p + 1, NJ, (r == sk)>(Y[r], Y[sk], l);
+                row_update<k, (r == sk), C - 1 - q, NJ - 1 - p>(X[r] + q + 1, X[sk] + q + 1, Y[r] + p + 1,
+                                                               Y[sk] + p + 1, l);
             });
         });
-        sfor<sk, S>([&](auto R) {
-            LT v = X[R][0];
-            sfor<1, C>([&](auto Q) { v = lane_in(lanes_in<L>(16 * Q, 16 * Q + 15)) ? X[R][Q] : v; });
-            Y[R][p] = v;
-        });
+        if constexpr (!BACK_EACH) {
+            sfor<sk, S>([&](auto R) {
+                LT v = opq(X[R][0]);
+                sfor<1, C>([&](auto Q) {
+                    const LT x = opq(X[R][Q]);
+                    v = lane_in(lanes_in<L>(16 * Q, 16 * Q + 15)) ? x : v;
+                });
+                Y[R][p] = v;
+            });
+        }
     };
     // nv tested once per 8 steps, as in steps8
     sfor<0, (NJ * C + 7) / 8>([&](auto G) {
@@ -1693,7 +1733,7 @@ __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
             LT l = z.M[0][k] * rinv;
             l = gt ? l : LT(0);
             z.M[0][k] = ge ? l : z.M[0][k];   // the pivot's own place is 0 (tri_solve)
-            row_update<k, k + 1, NVP, true>(z.M[0], z.M[0], l);
+            row_update<k, true, 0, NVP - 1 - k, 4>(z.M[0], z.M[0], z.M[0] + k + 1, z.M[0] + k + 1, l);
             return;
         }
         // each candidate against the pivot in its own lane, so no reduction per step: the
@@ -1715,13 +1755,17 @@ __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
 template <int NVP, int L, class LT>
 __device__ __forceinline__ void factor_M(const Ctx &c, Zone<NVP, L, LT> &z, double gamma)
 {
-    form_M(c, z, gamma);
     if constexpr (kept_order<NVP, L, LT>()) {
         if (!c.lu_blocked) {
+            form_M<M_KEPT>(c, z, gamma);
             if (lu_kept_order(c, z)) return;
             z.pivlane = c.gl;
-            form_M(c, z, gamma);
+            form_M<M_AGAIN>(c, z, gamma);
+        } else {
+            form_M<M_PLAIN>(c, z, gamma);
         }
+    } else {
+        form_M<M_PLAIN>(c, z, gamma);
     }
     lu_factor(c, z);
 }
@@ -1738,7 +1782,7 @@ __device__ __forceinline__ void lu_solve(const Ctx &c, const Zone<NVP, L, LT> &z
         const int src = (int)(threadIdx.x & (64 - L)) + z.pivlane;
         const double bp = gather(b[0], src);
         LT v = MIXED ? (LT)(bp * (double)z.rs[0]) : (LT)bp;
-        if constexpr (dpp_solve<L, LT>()) {
+        if constexpr (dpp_solve<L>()) {
             tri_solve<NVP, L>(nv, v, z.M[0], z.dinv[0]);
         } else {
             steps8<NVP>(nv, [&](auto K) {
