@@ -394,45 +394,6 @@ __device__ __forceinline__ double step_factor(double x, int k)
 
 // --------------------------------------------------------- BDF coefficients
 
-// l_j(q): coefficients of prod_{i<=q} (1 + x/i) divided by H_q (so l_1 = 1).
-__device__ __forceinline__ double lcoef(int q, int j)
-{
-    // rows q = 1..5, columns j = 0..5, exact rationals rounded once
-    const double t[5][6] = {
-        {1.0, 1.0, 0.0, 0.0, 0.0, 0.0},
-        {2.0 / 3.0, 1.0, 1.0 / 3.0, 0.0, 0.0, 0.0},
-        {6.0 / 11.0, 1.0, 6.0 / 11.0, 1.0 / 11.0, 0.0, 0.0},
-        {12.0 / 25.0, 1.0, 7.0 / 10.0, 1.0 / 5.0, 1.0 / 50.0, 0.0},
-        {60.0 / 137.0, 1.0, 225.0 / 274.0, 85.0 / 274.0, 15.0 / 274.0, 1.0 / 274.0}};
-    double v = t[0][j];
-#pragma unroll
-    for (int r = 1; r < 5; ++r)
-        if (q == r + 1) v = t[r][j];
-    return v;
-}
-
-// l_0(q) = 1 / H_q (the divisions are done by the compiler)
-__device__ __forceinline__ double inv_harmonic(int q)
-{
-    double v = 1.0;
-    v = (q == 2) ? 1.0 / 1.5 : v;
-    v = (q == 3) ? 1.0 / (11.0 / 6.0) : v;
-    v = (q == 4) ? 1.0 / (25.0 / 12.0) : v;
-    v = (q == 5) ? 1.0 / (137.0 / 60.0) : v;
-    return v;
-}
-
-// H_q = 1 / l_0(q)
-__device__ __forceinline__ double harmonic(int q)
-{
-    double v = 1.0;
-    v = (q == 2) ? 1.5 : v;
-    v = (q == 3) ? 11.0 / 6.0 : v;
-    v = (q == 4) ? 25.0 / 12.0 : v;
-    v = (q == 5) ? 137.0 / 60.0 : v;
-    return v;
-}
-
 // c(n, j) = [x^j] x (x+1) ... (x+n-1), n = 2..6
 __device__ __forceinline__ double stirling(int n, int j)
 {
@@ -449,19 +410,6 @@ __device__ __forceinline__ double stirling(int n, int j)
     return v;
 }
 
-// (2/3 - 1e-6)^n for n = 1..6
-__device__ __forceinline__ double cpow23(int n)
-{
-    const double c = 2.0 / 3.0 - 1e-6;
-    double v = c;
-    v = (n >= 2) ? v * c : v;
-    v = (n >= 3) ? v * c : v;
-    v = (n >= 4) ? v * c : v;
-    v = (n >= 5) ? v * c : v;
-    v = (n >= 6) ? v * c : v;
-    return v;
-}
-
 __device__ __forceinline__ double factorial(int n)
 {
     double v = 1.0;
@@ -471,6 +419,46 @@ __device__ __forceinline__ double factorial(int n)
     v = (n == 5) ? 120.0 : v;
     v = (n == 6) ? 720.0 : v;
     return v;
+}
+
+// What a step needs of its order q, as one row of a table in memory: selects among the orders'
+// constants took 150 vector instructions a step (the constants are 64 bits, the order differs
+// between the zones of a wave), a row is a few loads that the norms before their use cover.  The
+// entries are the same doubles as the expressions they replace.
+struct OrderRow {
+    double l0, H;            // 1 / H_q, H_q
+    double l[QMAX];          // l_1 .. l_5 (0 past q)
+    double cq, cm, cp;       // order tests: (2/3 - 1e-6)^n (1 + 1e-9), n = q + 1, q, q + 2
+    double fm;               // (q - 1)!
+    double r1, r2;           // 1 / (q + 1), 1 / (q + 2), rounded
+    double pad[2];
+};
+constexpr double c23(int n) { return n == 1 ? 2.0 / 3.0 - 1e-6 : c23(n - 1) * (2.0 / 3.0 - 1e-6); }
+constexpr double c23m(int n) { return c23(n) * (1.0 + 1e-9); }
+static __device__ const OrderRow ORDER_ROWS[QMAX] = {
+    {1.0, 1.0, {1.0, 0.0, 0.0, 0.0, 0.0}, c23m(2), c23m(1), c23m(3), 1.0, 1.0 / 2.0, 1.0 / 3.0, {}},
+    {1.0 / 1.5, 1.5, {1.0, 1.0 / 3.0, 0.0, 0.0, 0.0}, c23m(3), c23m(2), c23m(4), 1.0, 1.0 / 3.0, 1.0 / 4.0, {}},
+    {1.0 / (11.0 / 6.0), 11.0 / 6.0, {1.0, 6.0 / 11.0, 1.0 / 11.0, 0.0, 0.0}, c23m(4), c23m(3), c23m(5), 2.0,
+     1.0 / 4.0, 1.0 / 5.0, {}},
+    {1.0 / (25.0 / 12.0), 25.0 / 12.0, {1.0, 7.0 / 10.0, 1.0 / 5.0, 1.0 / 50.0, 0.0}, c23m(5), c23m(4), c23m(6),
+     6.0, 1.0 / 5.0, 1.0 / 6.0, {}},
+    {1.0 / (137.0 / 60.0), 137.0 / 60.0, {1.0, 225.0 / 274.0, 85.0 / 274.0, 15.0 / 274.0, 1.0 / 274.0}, c23m(6),
+     c23m(5), c23m(6), 24.0, 1.0 / 6.0, 1.0 / 7.0, {}}};
+
+// The row of order q, read at this point of the program.
+__device__ __forceinline__ const __attribute__((address_space(1))) OrderRow &order_row(int q)
+{
+    const OrderRow *p = ORDER_ROWS + (q - 1);
+    return *(const __attribute__((address_space(1))) OrderRow *)p;
+}
+
+// x / d as the division rounds it, for d a small integer with r = 1/d rounded: the product
+// corrected by its exact remainder (inf and NaN pass through).
+__device__ __forceinline__ double div_small(double x, double d, double r)
+{
+    const double q = x * r;
+    const double y = fma(fma(-d, q, x), r, q);
+    return (x < __builtin_inf()) ? y : x;
 }
 
 // ------------------------------------------------------------- zone state
@@ -2142,7 +2130,7 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
     if constexpr (VC) {
         vc_coefficients(c, z.q, h, l0, ediv);
     } else {
-        l0 = inv_harmonic(z.q);
+        l0 = order_row(z.q).l0;
         ediv = (double)(z.q + 1);
     }
     const double gamma = h * l0;
@@ -2193,11 +2181,26 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
         return RUNNING;
     }
 
-    const double err = wrms(c, z, z.dy) / ediv;
+    // (an opaque order keeps the loads here: earlier, the row would hold registers through Newton)
+    int qr = z.q;
+    asm volatile("" : "+v"(qr));
+    const auto &O = order_row(qr);
+    const double o_r1 = O.r1, o_H = O.H;
+    double o_l[QMAX + 1];
+    if constexpr (!VC) {
+#pragma unroll
+        for (int j = 1; j <= QMAX; ++j) o_l[j] = O.l[j - 1];
+    }
+    const double dyn = wrms(c, z, z.dy);
+    const double err = VC ? dyn / ediv : div_small(dyn, ediv, o_r1);
     // Non-negativity of the abundances: a step that takes a species below -atol fails
     // like an error test and is cut to 0.9 of its feasible fraction (from the saved Z_0).
+    // Rare: looked for lane by lane, and only then reduced over the group.
     double feas = 1.0;
-    {
+    bool below = false;
+#pragma unroll
+    for (int s = 0; s < RPL; ++s) below = below || (row_of<NVP, L>(c, s) < c.ns && z.y[s] < -z.atol);
+    if (__ballot(below)) {
         const double *zs = c.S + c.lay.zs;
 #pragma unroll
         for (int s = 0; s < RPL; ++s) {
@@ -2245,11 +2248,12 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
     }
 
     // accept: Z_j += l_j e with e = dy / l_0, Z_0 = y
-    const double H = VC ? 1.0 / l0 : harmonic(z.q);
+    // (without the variable coefficients, the columns past q add 0)
+    const double H = VC ? 1.0 / l0 : o_H;
 #pragma unroll
     for (int j = 1; j <= QMAX; ++j) {
-        const double lj = VC ? c.S[c.lay.vc + VC_L + j] : lcoef(z.q, j);
-        const bool in = j <= z.q;
+        const double lj = VC ? c.S[c.lay.vc + VC_L + j] : o_l[j];
+        const bool in = !VC || j <= z.q;
 #pragma unroll
         for (int s = 0; s < RPL; ++s) {
             const double u = z.Z[j][s] + lj * (z.dy[s] * H);
@@ -2281,7 +2285,7 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
         // eta_p = 1 / ((b E_p)^(1/(p+1)) + 1e-6) >= 1.5  iff  b E_p <= (2/3 - 1e-6)^(p+1).
         // The powers are evaluated only when some order may pass (a conservative
         // pre-filter, so every decision is the one the plain formula gives).
-        const double cq = cpow23(q + 1) * (1.0 + 1e-9);
+        const double cq = O.cq;
         bool may = 6.0 * err <= cq;
         double Em = 0.0, Ep = 0.0;
         if (q > 1) {
@@ -2296,15 +2300,15 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
                 }
                 zq[s] = v;
             }
-            Em = factorial(q - 1) * wrms(c, z, zq);
-            may = may || (6.0 * Em <= cpow23(q) * (1.0 + 1e-9));
+            Em = O.fm * wrms(c, z, zq);
+            may = may || (6.0 * Em <= O.cm);
         }
         if (q < QMAX) {
             double dd[RPL];
 #pragma unroll
             for (int s = 0; s < RPL; ++s) dd[s] = z.dy[s] - z.dyp[s];
-            Ep = wrms(c, z, dd) / (double)(q + 2);
-            may = may || (10.0 * Ep <= cpow23(q + 2) * (1.0 + 1e-9));
+            Ep = div_small(wrms(c, z, dd), (double)(q + 2), O.r2);
+            may = may || (10.0 * Ep <= O.cp);
         }
         double best = 0.0;
         int qnew = q;
