@@ -431,7 +431,7 @@ struct OrderRow {
     double cq, cm, cp;       // order tests: (2/3 - 1e-6)^n (1 + 1e-9), n = q + 1, q, q + 2
     double fm;               // (q - 1)!
     double r1, r2;           // 1 / (q + 1), 1 / (q + 2), rounded
-    double pad[2];
+    double pad[3];
 };
 constexpr double c23(int n) { return n == 1 ? 2.0 / 3.0 - 1e-6 : c23(n - 1) * (2.0 / 3.0 - 1e-6); }
 constexpr double c23m(int n) { return c23(n) * (1.0 + 1e-9); }
@@ -448,7 +448,8 @@ static __device__ const OrderRow ORDER_ROWS[QMAX] = {
 // The row of order q, read at this point of the program.
 __device__ __forceinline__ const __attribute__((address_space(1))) OrderRow &order_row(int q)
 {
-    const OrderRow *p = ORDER_ROWS + (q - 1);
+    static_assert(sizeof(OrderRow) == 128, "rows by a shift");
+    const char *p = (const char *)ORDER_ROWS + (((unsigned)q - 1u) << 7);
     return *(const __attribute__((address_space(1))) OrderRow *)p;
 }
 
@@ -559,10 +560,9 @@ __device__ __forceinline__ double wrms(const Ctx &c, const Zone<NVP, L, LT> &z,
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < RPL; ++k) {
-        if (row_of<NVP, L>(c, k) < c.nv) {
-            double x = v[k] * z.iw[k];
-            s = fma(x, x, s);
-        }
+        // rows past nv hold 0 in every vector (and iw)
+        const double x = v[k] * z.iw[k];
+        s = fma(x, x, s);
     }
     s = greduce<L>(s, OpAdd());
     return rms_of_sum(s, c.nv);
@@ -972,6 +972,13 @@ template <int L>
 constexpr unsigned long long lanes_in(int a, int b)
 {
     return group_lanes<L>((b - a == 63) ? ~0ull : (((1ull << (b - a + 1)) - 1ull) << a));
+}
+
+// Whether this lane is in the wave mask m (a constant), as a scalar mask made where it is used:
+// a compare of the lane number would be shared between steps and spilled to vector registers.
+__device__ __forceinline__ bool lane_in(unsigned long long m)
+{
+    return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
 // Value of the 16-lane block B of the group in every block, lane by lane.
@@ -1499,13 +1506,6 @@ __device__ __forceinline__ void lu_factor(const Ctx &c, Zone<NVP, L, LT> &z)
 // solutions are the same for every pivot order.
 constexpr float PIV_KEEP = 0.5f;
 
-// Whether this lane is in the wave mask m (a constant), as a scalar mask made where it is used:
-// a compare of the lane number would be shared between steps and spilled to vector registers.
-__device__ __forceinline__ bool lane_in(unsigned long long m)
-{
-    return __builtin_amdgcn_inverse_ballot_w64(m);
-}
-
 // d_j -= l p_j for N columns, p_j taken from lane K % 16 of the lane's own 16-lane row: one
 // v_fmac with row_newbcast a column.  The compiler makes a broadcast and an FMA of it (two vector
 // instructions in FP32; in FP64, where it moves the halves apart, three).  The leading wait
@@ -1726,12 +1726,12 @@ __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
         }
         // each candidate against the pivot in its own lane, so no reduction per step: the
         // rows of lanes below k are eliminated, lanes past nvp hold zero rows (a NaN fails)
-        if (c.gl > k) bad = bad || !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP));
+        const bool gt = lane_in(lanes_in<L>(0, L - 1) & ~lanes_in<L>(0, k));
+        bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
         const LT rinv = recip(piv);
-        if (c.gl == k) z.dinv[0] = rinv;
-        const bool act = c.gl > k;
-        const LT l = act ? z.M[0][k] * rinv : LT(0);
-        if (act) z.M[0][k] = l;
+        if (lane_in(lanes_in<L>(k, k))) z.dinv[0] = rinv;
+        const LT l = gt ? z.M[0][k] * rinv : LT(0);
+        if (gt) z.M[0][k] = l;
         sfor<k + 1, NVP>([&](auto J) { z.M[0][J] = fma(-l, bcast_k<L, k>(z.M[0][J]), z.M[0][J]); });
     });
     return !gany<L>(bad);
@@ -1776,12 +1776,12 @@ __device__ __forceinline__ void lu_solve(const Ctx &c, const Zone<NVP, L, LT> &z
             steps8<NVP>(nv, [&](auto K) {
                 constexpr int k = K;
                 const LT yk = bcast_k<L, k>(v);
-                if (after(c.gl, v) > k) v = fma(-z.M[0][k], yk, v);
+                if (lane_in(lanes_in<L>(0, L - 1) & ~lanes_in<L>(0, k))) v = fma(-z.M[0][k], yk, v);
             });
             steps8<NVP, true>(nv, [&](auto K) {
                 constexpr int k = K;
                 const LT xk = bcast_k<L, k>(v * z.dinv[0]);
-                if (after(c.gl, v) < k) v = fma(-z.M[0][k], xk, v);
+                if (lane_in(lanes_in<L>(0, k) & ~lanes_in<L>(k, k))) v = fma(-z.M[0][k], xk, v);
             });
         }
         double x = c.gl < nv ? (double)(v * z.dinv[0]) : 0.0;
@@ -2191,7 +2191,10 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
 #pragma unroll
         for (int j = 1; j <= QMAX; ++j) o_l[j] = O.l[j - 1];
     }
+    double o_cq = O.cq, o_cm = O.cm, o_cp = O.cp, o_fm = O.fm, o_r2 = O.r2;
     const double dyn = wrms(c, z, z.dy);
+    // one wait for the whole row, here: the loads would sink to each use otherwise
+    o_cq = opq(o_cq); o_cm = opq(o_cm); o_cp = opq(o_cp); o_fm = opq(o_fm); o_r2 = opq(o_r2);
     const double err = VC ? dyn / ediv : div_small(dyn, ediv, o_r1);
     // Non-negativity of the abundances: a step that takes a species below -atol fails
     // like an error test and is cut to 0.9 of its feasible fraction (from the saved Z_0).
@@ -2285,7 +2288,7 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
         // eta_p = 1 / ((b E_p)^(1/(p+1)) + 1e-6) >= 1.5  iff  b E_p <= (2/3 - 1e-6)^(p+1).
         // The powers are evaluated only when some order may pass (a conservative
         // pre-filter, so every decision is the one the plain formula gives).
-        const double cq = O.cq;
+        const double cq = o_cq;
         bool may = 6.0 * err <= cq;
         double Em = 0.0, Ep = 0.0;
         if (q > 1) {
@@ -2300,15 +2303,15 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
                 }
                 zq[s] = v;
             }
-            Em = O.fm * wrms(c, z, zq);
-            may = may || (6.0 * Em <= O.cm);
+            Em = o_fm * wrms(c, z, zq);
+            may = may || (6.0 * Em <= o_cm);
         }
         if (q < QMAX) {
             double dd[RPL];
 #pragma unroll
             for (int s = 0; s < RPL; ++s) dd[s] = z.dy[s] - z.dyp[s];
-            Ep = div_small(wrms(c, z, dd), (double)(q + 2), O.r2);
-            may = may || (10.0 * Ep <= O.cp);
+            Ep = div_small(wrms(c, z, dd), (double)(q + 2), o_r2);
+            may = may || (10.0 * Ep <= o_cp);
         }
         double best = 0.0;
         int qnew = q;
