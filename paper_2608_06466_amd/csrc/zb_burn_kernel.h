@@ -392,6 +392,19 @@ __device__ __forceinline__ double step_factor(double x, int k)
     return (d < __builtin_inf()) ? zbm::recip_from(d, __builtin_amdgcn_rcp(d)) : 1.0 / d;
 }
 
+// The temperature's logarithm: log_normal where every zone of the wave has a positive normal
+// temperature (the same bits), else log_series with its special values.
+__device__ __forceinline__ double log_T(double T)
+{
+    if (__ballot(!__builtin_isfpclass(T, 0x100))) return zbm::log_series(T);   // +normal
+    return zbm::log_normal(
+        __builtin_amdgcn_frexp_mant(T), __builtin_amdgcn_frexp_exp(T), [](double d) { return __builtin_amdgcn_rcp(d); },
+        [](double c) {
+            asm("" : "+s"(c));
+            return c;
+        });
+}
+
 // --------------------------------------------------------- BDF coefficients
 
 // c(n, j) = [x^j] x (x+1) ... (x+n-1), n = 2..6
@@ -451,15 +464,6 @@ __device__ __forceinline__ const __attribute__((address_space(1))) OrderRow &ord
     static_assert(sizeof(OrderRow) == 128, "rows by a shift");
     const char *p = (const char *)ORDER_ROWS + (((unsigned)q - 1u) << 7);
     return *(const __attribute__((address_space(1))) OrderRow *)p;
-}
-
-// x / d as the division rounds it, for d a small integer with r = 1/d rounded: the product
-// corrected by its exact remainder (inf and NaN pass through).
-__device__ __forceinline__ double div_small(double x, double d, double r)
-{
-    const double q = x * r;
-    const double y = fma(fma(-d, q, x), r, q);
-    return (x < __builtin_inf()) ? y : x;
 }
 
 // ------------------------------------------------------------- zone state
@@ -626,7 +630,7 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
     double lnT = 0.0, iT = 0.0;
     if constexpr (RPL == 1) {
         if (N.thermal) {
-            lnT = zbm::log_series(Tg);
+            lnT = log_T(Tg);
             iT = zbm::recip_from(Tg, __builtin_amdgcn_rcp(Tg));
         }
     }
@@ -650,7 +654,7 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
 
     if (RPL > 1 && N.thermal) {
         double T = ybuf[N.ns];
-        lnT = zbm::log_series(T);
+        lnT = log_T(T);
         // the hardware reciprocal refined (zb_stepmath.h): on 2^20 zones of the 14-variable
         // network the results came out bitwise as with the division, at fewer instructions
         iT = zbm::recip_from(T, __builtin_amdgcn_rcp(T));
@@ -2195,7 +2199,7 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
     const double dyn = wrms(c, z, z.dy);
     // one wait for the whole row, here: the loads would sink to each use otherwise
     o_cq = opq(o_cq); o_cm = opq(o_cm); o_cp = opq(o_cp); o_fm = opq(o_fm); o_r2 = opq(o_r2);
-    const double err = VC ? dyn / ediv : div_small(dyn, ediv, o_r1);
+    const double err = VC ? dyn / ediv : zbm::div_small(dyn, ediv, o_r1);
     // Non-negativity of the abundances: a step that takes a species below -atol fails
     // like an error test and is cut to 0.9 of its feasible fraction (from the saved Z_0).
     // Rare: looked for lane by lane, and only then reduced over the group.
@@ -2310,7 +2314,7 @@ __device__ __forceinline__ int zone_attempt(const Ctx &c, Zone<NVP, L, LT> &z)
             double dd[RPL];
 #pragma unroll
             for (int s = 0; s < RPL; ++s) dd[s] = z.dy[s] - z.dyp[s];
-            Ep = div_small(wrms(c, z, dd), (double)(q + 2), o_r2);
+            Ep = zbm::div_small(wrms(c, z, dd), (double)(q + 2), o_r2);
             may = may || (10.0 * Ep <= o_cp);
         }
         double best = 0.0;

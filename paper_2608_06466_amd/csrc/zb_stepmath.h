@@ -53,4 +53,13 @@ ZB_SM_FN double root_from(double x, int k, double y0, Rcp rcp)
     return y;
 }
 
+// x / d as the division rounds it, for x >= 0 (or NaN) and d a small integer with r = 1/d rounded:
+// the product corrected by its exact remainder (inf and NaN pass through).
+ZB_SM_FN double div_small(double x, double d, double r)
+{
+    const double q = x * r;
+    const double y = __builtin_fma(__builtin_fma(-d, q, x), r, q);
+    return (x < __builtin_inf()) ? y : x;
+}
+
 }  // namespace zbm
