@@ -606,10 +606,7 @@ __device__ __forceinline__ void eval(const Ctx &c, Zone<NVP, L, LT> &z, const do
     if constexpr (QMX > 0) {
         const int i0 = row_of<NVP, L>(c, 0);
         const int4 *l0 = (const int4 *)(N.inv + (i0 < N.ns ? i0 : 0) * N.inv_len);
-        sfor<0, QMX>([&](auto P) {
-            pre[P] = make_int4(0, 0, 0, 0);
-            if (use_pre && P < n4) pre[P] = gload(l0 + P);
-        });
+        sfor<0, QMX>([&](auto P) { pre[P] = gload(l0 + P); });   // past the row: unused (the table has room)
     }
     unsigned nab = 0;
     double4 npr = make_double4(0.0, 0.0, 0.0, 0.0);
@@ -2001,8 +1998,12 @@ template <int NVP, int L, class LT>
 __device__ __forceinline__ bool newton(const Ctx &c, Zone<NVP, L, LT> &z, double l0, double h, double tau)
 {
     constexpr int RPL = Zone<NVP, L, LT>::RPL;
-    const double rc = h * l0 / z.gamma_m;
-    const double cscale = (rc != 1.0) ? 2.0 / (1.0 + rc) : 1.0;
+    // (a Jacobian every step: the factors are this gamma's, the scale is 1)
+    double cscale = 1.0;
+    if (c.jac_policy != 0) {
+        const double rc = h * l0 / z.gamma_m;
+        cscale = (rc != 1.0) ? 2.0 / (1.0 + rc) : 1.0;
+    }
 #pragma unroll
     for (int s = 0; s < RPL; ++s) {
         z.y[s] = z.Z[0][s];
@@ -2018,7 +2019,7 @@ __device__ __forceinline__ bool newton(const Ctx &c, Zone<NVP, L, LT> &z, double
 #pragma unroll
         for (int s = 0; s < RPL; ++s) b[s] = -(z.dy[s] - l0 * (h * z.f[s] - z.Z[1][s]));
         lu_solve(c, z, b);
-        if (cscale != 1.0) {
+        if (c.jac_policy != 0 && cscale != 1.0) {
 #pragma unroll
             for (int s = 0; s < RPL; ++s) b[s] *= cscale;
         }

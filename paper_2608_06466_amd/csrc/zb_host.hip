@@ -167,7 +167,8 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     int inv_len = 4;
     for (int i = 0; i < ns; ++i) inv_len = std::max<int>(inv_len, (int)inv[i].size());
     inv_len = (inv_len + 3) & ~3;   // the kernels take four entries per load
-    std::vector<unsigned> invf((size_t)ns * inv_len, (unsigned)(8 * nr));   // padding: the 0 slot
+    // padding: the 0 slot; room for the three loads the 14-row kernels make of every row
+    std::vector<unsigned> invf((size_t)ns * inv_len + 12, (unsigned)(8 * nr));
     for (int i = 0; i < ns; ++i) std::copy(inv[i].begin(), inv[i].end(), invf.begin() + (size_t)i * inv_len);
     // the reactions each species is a reactant of (DevNet::con)
     std::vector<std::vector<std::pair<unsigned, double>>> con(ns);
