@@ -2613,7 +2613,7 @@ constexpr int min_waves_per_eu()
     // the 8-row kernel fits three waves with a Jacobian every step
     if (NVP == 8 && L == 8 && (JP == METHOD_BDF || JP == METHOD_BDF_VC)) return 3;
     // the 14-row kernels with a Jacobian every step: three waves at 168 VGPRs, with the history
-    // copy in registers.  FP64 (160 bytes a lane spilled; 214 VGPRs unbounded): 50021 zones 115 ->
+    // copy in registers.  FP64 (148 bytes a lane spilled; 214 VGPRs unbounded): 50021 zones 115 ->
     // 103 ms, 100003 of the 20-reaction network 62.6 -> 56.5; 512 zones, one wave a SIMD, 17.2 ->
     // 18.8.  The mixed reuse kernels too: 11 % faster (fixed-coefficient form) and 2 %
     // (variable-coefficient form).  Measured slower with a third wave: the variable form with a
@@ -2622,7 +2622,7 @@ constexpr int min_waves_per_eu()
         (JP == METHOD_BDF ||
          (sizeof(LT) == 4 && (JP == METHOD_BDF_REUSE || JP == METHOD_BDF_VC_REUSE))))
         return 3;
-    // the mixed 22-row kernel with a Jacobian every step (148 bytes spilled): 14 % faster
+    // the mixed 22-row kernel with a Jacobian every step (140 bytes spilled): 14 % faster
     if (NVP == 22 && L == 32 && sizeof(LT) == 4 && JP == METHOD_BDF) return 3;
     // RKC keeps no matrix: four waves fit (the compiler would take two registers more)
     if (JP == METHOD_RKC) return 4;

@@ -97,3 +97,25 @@ def test_no_reactions(zbm, ns, precision):
     assert zb.sync(ctx) == 0
     assert np.array_equal(t.cpu().numpy(), st)
     net.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nv,lanes", [(6, 16), (8, 16), (12, 32), (16, 32), (24, 64), (40, 64)])
+def test_solve_skips_whole_chunks(zbm, nv, lanes, precision):
+    """Networks that leave whole 8-step chunks of the kernel's rows unused (8 variables on the
+    14-row kernel, 16 on the 22-row one): the solves take the chunks that the LU took, and no
+    pivot of a skipped row, which is never set.  Both Jacobian policies, against the oracle."""
+    zb, ctx = zbm
+    net_d = W.random_network(nv - 1, 2 * nv, 900 + nv)
+    st = W.random_zones(net_d, 24, 901 + nv, T_range=(90.0, 1000.0), T_dist="loguniform")
+    net = zb.Network(ctx, net_d)
+    for policy in (0, 1):
+        t = torch.tensor(st, device="cuda:0")
+        status, stats = zb.burn(ctx, net, t, 1.0, 1e-8, 1e-12, precision=precision, lanes=lanes,
+                                jac_policy=policy)
+        assert zb.sync(ctx) == 0
+        check(f"nv {nv} on {lanes} lanes {precision} policy {policy}",
+              (t.cpu().numpy(), status.cpu().numpy(), stats.cpu().numpy()),
+              oracle.burn(net_d, st, 1.0, 1e-8, 1e-12, jac_policy=policy), 1e-8, 1e-12, nv,
+              fine=oracle.burn(net_d, st, 1.0, 1e-10, 1e-14, jac_policy=policy, max_steps=10000000), state_in=st)
+    net.close()
