@@ -337,12 +337,17 @@ int zbh::lanes_for(zb_context *ctx, const zb_network *net, int prec, const zb_op
             return auto_mfma ? t.auto_lanes : t.lanes;
     // The per-zone LDS area holds the reaction columns (5 doubles a reaction) once per zone of
     // the wave, so a small network with many reactions needs wider groups: widen until two
-    // waves fit a CU.
+    // waves fit a CU.  One mapping serves every method of a network, so in FP64 the reuse
+    // kernel's area counts: its history copy is in LDS, and where only the every-step kernel's
+    // (in registers) leaves room for two, one wave is slow (14 variables, 455 reactions, 2011
+    // zones with rate scales on 16 and 32 lanes: reuse 135 and 80 ms, variable form 145 and 98;
+    // every step without rate scales 77 and 59, with them 82 and 95).
+    const int method = prec == ZB_MIXED ? METHOD_BDF : METHOD_BDF_REUSE;
     const int steps[] = {1, 4, 8, 16, 32, 64};
     const int L0 = default_lanes(net->dn.nv);
     for (int L : steps) {
         if (L < L0) continue;
-        const KernelInfo *k = find_kernel(net->dn.nv, L, prec == ZB_MIXED, 0);
+        const KernelInfo *k = find_kernel(net->dn.nv, L, prec == ZB_MIXED, method);
         if (k && launch_lds(k, net->dn.nr) <= 80 * 1024) return L;
     }
     return 64;
