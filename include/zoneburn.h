@@ -345,12 +345,13 @@ zb_err zb_autotune_candidates(zb_context *ctx, const zb_network *net, const doub
 /* The context's autotuned choices (zb_autotune, zb_autotune_candidates) as a JSON file at
    `path` (HOST string): one entry per (network size, reactions, precision) with the lanes per
    zone of the vector LU and the (lanes, LU) pair of ZB_LU_AUTO, keyed by the device's
-   architecture name and the HIP runtime version.  The file is written beside `path` and
+   architecture name, the HIP runtime version and an id of the kernels timed.  The file is written beside `path` and
    renamed over it.  ZB_EINVAL when it cannot be written. */
 zb_err zb_tune_save(zb_context *ctx, const char *path);
 /* Adds the choices of a file written by zb_tune_save to this context's table (replacing
    entries of the same key); *loaded (optional) receives the number applied.  A file from
-   another architecture or HIP runtime version applies nothing (*loaded = 0, ZB_OK), and
+   another architecture, HIP runtime version or build of the kernels (or one that names no
+   kernels) holds timings of something else and applies nothing (*loaded = 0, ZB_OK), and
    entries naming a kernel this library does not hold are skipped.  ZB_EINVAL for a missing,
    unreadable, malformed or over-1-MiB file, or values out of range (the table is then left
    as it was). */

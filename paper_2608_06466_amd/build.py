@@ -3,6 +3,7 @@
     python -m paper_2608_06466_amd.build [--jobs N] [--verbose]
 """
 import argparse
+import hashlib
 import os
 import subprocess
 import sys
@@ -52,9 +53,23 @@ SCHED = {
 }
 
 
+def kernels_id():
+    """Identifies the burn kernels of a build (their sources, flags and scheduling): saved tuning
+    files carry it, since other kernels have other fastest mappings."""
+    h = hashlib.sha256(repr(([f for f in FLAGS if not os.path.isabs(f)], sorted(SCHED.items()))).encode())
+    for f in sorted(os.listdir(CSRC)):
+        if f.startswith("zb_k") and f.endswith(".hip") or f in (
+                "zb_burn_kernel.h", "zb_internal.h", "zb_log.h", "zb_stepmath.h"):
+            with open(os.path.join(CSRC, f), "rb") as s:
+                h.update(s.read())
+    return h.hexdigest()[:16]
+
+
 def _compile(src, verbose):
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     extra = ["-mllvm", f"-amdgpu-sched-strategy={SCHED[src]}"] if src in SCHED else []
+    if src == "zb_host.hip":
+        extra.append(f'-DZB_KERNELS_ID="{kernels_id()}"')
     cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)

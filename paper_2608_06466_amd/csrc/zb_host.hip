@@ -1116,6 +1116,10 @@ extern "C" zb_err zb_autotune_candidates(zb_context *ctx, const zb_network *net,
 
 // ------------------------------------------------------------ tuning cache
 
+#ifndef ZB_KERNELS_ID
+#error "ZB_KERNELS_ID: the id of the kernel sources and flags, set by the build"
+#endif
+
 extern "C" zb_err zb_tune_save(zb_context *ctx, const char *path)
 {
     if (!ctx || !path) return fail(ZB_EINVAL, "NULL argument");
@@ -1126,7 +1130,7 @@ extern "C" zb_err zb_tune_save(zb_context *ctx, const char *path)
         std::lock_guard<std::mutex> lk(ctx->mu);
         es = ctx->tuned;
     }
-    const std::string text = tune_json(ctx->arch, rt, es);
+    const std::string text = tune_json(ctx->arch, rt, es, ZB_KERNELS_ID);
     // written next to the target and renamed over it, so a reader never sees half a file
     const std::string tmp = std::string(path) + ".tmp";
     FILE *f = fopen(tmp.c_str(), "wb");
@@ -1162,14 +1166,14 @@ extern "C" zb_err zb_tune_load(zb_context *ctx, const char *path, int32_t *loade
     const bool rd_err = ferror(f) != 0;
     fclose(f);
     if (rd_err) return fail(ZB_EINVAL, "cannot read %s", path);
-    std::string arch, err;
+    std::string arch, kernels, err;
     int rt_file = 0;
     std::vector<TuneEntry> es;
-    if (!tune_parse(text, NVMAX, RMAX, arch, rt_file, es, err)) return fail(ZB_EINVAL, "%s: %s", path, err.c_str());
+    if (!tune_parse(text, NVMAX, RMAX, arch, rt_file, es, err, &kernels))
+        return fail(ZB_EINVAL, "%s: %s", path, err.c_str());
     int rt = 0;
     HIP_TRY(hipRuntimeGetVersion(&rt));
-    // timings from another GPU or HIP runtime say nothing about this one
-    if (arch != ctx->arch || rt_file != rt) return ZB_OK;
+    if (!tune_applies(arch, rt_file, kernels, ctx->arch, rt, ZB_KERNELS_ID)) return ZB_OK;
     int applied = 0;
     std::lock_guard<std::mutex> lk(ctx->mu);
     for (const TuneEntry &e : es) {

@@ -1,14 +1,15 @@
-// The autotuner's choices as a JSON file, so that a later process on the same kind of GPU and
-// the same HIP runtime starts from them instead of timing again.  Host-only and free of HIP,
+// The autotuner's choices as a JSON file, so that a later process on the same kind of GPU, the
+// same HIP runtime and the same kernels starts from them instead of timing again.  Host-only and free of HIP,
 // so that a CPU test (under the sanitizers) covers the writer, the reader and its rejection of
 // malformed files.
 //
 // Format (one object; keys in any order, whitespace free):
 //   {"format": "zoneburn-tune-1", "arch": "<gcnArchName>", "hip_runtime": <int>,
-//    "entries": [{"nv": 14, "nr": 30, "precision": 1, "lanes": 16,
+//    "kernels": "<id of the kernels timed>", "entries": [{"nv": 14, "nr": 30, "precision": 1, "lanes": 16,
 //                 "auto_lanes": 16, "auto_lu": 0}, ...]}
 // An entry is keyed by (nv, nr, precision); lanes is the mapping with the vector LU, and
-// (auto_lanes, auto_lu) the pair for ZB_LU_AUTO.
+// (auto_lanes, auto_lu) the pair for ZB_LU_AUTO.  "kernels" is absent from files of libraries
+// that wrote none: those were timed on other kernels.
 #pragma once
 
 #include <stdint.h>
@@ -25,14 +26,17 @@ struct TuneEntry {
     int nv, nr, prec, lanes, auto_lanes, auto_lu;
 };
 
-inline std::string tune_json(const std::string &arch, int runtime, const std::vector<TuneEntry> &es)
+inline std::string tune_json(const std::string &arch, int runtime, const std::vector<TuneEntry> &es,
+                             const std::string &kernels = "")
 {
     std::string s = "{\"format\": \"zoneburn-tune-1\", \"arch\": \"";
     for (char ch : arch) {   // the architecture name is plain ASCII; anything else is dropped
         if (ch == '"' || ch == '\\' || (unsigned char)ch < 0x20 || (unsigned char)ch > 0x7e) continue;
         s += ch;
     }
-    s += "\", \"hip_runtime\": " + std::to_string(runtime) + ", \"entries\": [";
+    s += "\", \"hip_runtime\": " + std::to_string(runtime);
+    if (!kernels.empty()) s += ", \"kernels\": \"" + kernels + "\"";
+    s += ", \"entries\": [";
     for (size_t i = 0; i < es.size(); ++i) {
         const TuneEntry &e = es[i];
         char b[192];
@@ -234,9 +238,11 @@ class JReader {
 
 // Reads a file written by tune_json.  Entries must have every field, as integers in range:
 // nv 1..nv_max, nr 0..nr_max, precision 0/1, lanes and auto_lanes powers of two 1..64,
-// auto_lu 0/1; any other content is an error (err says which).
+// auto_lu 0/1; any other content is an error (err says which).  kernels (optional) receives the
+// id of the kernels timed, empty when the file has none.
 inline bool tune_parse(const std::string &text, int nv_max, int nr_max, std::string &arch,
-                       int &runtime, std::vector<TuneEntry> &out, std::string &err)
+                       int &runtime, std::vector<TuneEntry> &out, std::string &err,
+                       std::string *kernels = nullptr)
 {
     JVal root;
     JReader rd(text);
@@ -263,6 +269,8 @@ inline bool tune_parse(const std::string &text, int nv_max, int nr_max, std::str
     const JVal *rt = a ? field(root, "hip_runtime", JVal::INT) : nullptr;
     const JVal *es = rt ? field(root, "entries", JVal::ARR) : nullptr;
     if (!es) return false;
+    const JVal *kn = nullptr;
+    if (root.o.count("kernels") && !(kn = field(root, "kernels", JVal::STR))) return false;
     if (rt->i < 0 || rt->i > 0x7fffffff) {
         err = "hip_runtime out of range";
         return false;
@@ -294,8 +302,17 @@ inline bool tune_parse(const std::string &text, int nv_max, int nr_max, std::str
     }
     arch = a->s;
     runtime = (int)rt->i;
+    if (kernels) *kernels = kn ? kn->s : std::string();
     out.swap(got);
     return true;
+}
+
+// Timings of another GPU, HIP runtime or build of the kernels say nothing about this one: the
+// fastest mapping and LU change with each of them.
+inline bool tune_applies(const std::string &arch_file, int runtime_file, const std::string &kernels_file,
+                         const std::string &arch, int runtime, const std::string &kernels)
+{
+    return arch_file == arch && runtime_file == runtime && !kernels.empty() && kernels_file == kernels;
 }
 
 }  // namespace zbh

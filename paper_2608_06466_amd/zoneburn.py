@@ -457,7 +457,7 @@ def tune_save(ctx, path):
 
 def tune_load(ctx, path):
     """Loads choices saved by tune_save into the context; returns how many applied (0 for a
-    file from another GPU architecture or HIP runtime)."""
+    file from another GPU architecture, HIP runtime or build of the kernels)."""
     n = C.c_int32(0)
     _check(lib().zb_tune_load(ctx.h, os.fsencode(path), C.byref(n)), "zb_tune_load")
     return int(n.value)

@@ -1,5 +1,6 @@
 """The lanes per zone chosen when the caller does not: a zone's LDS area grows with its reactions,
-and the group widens where two waves of the kernels would no longer fit a CU."""
+and the group widens where two waves of the kernels would no longer fit a CU; a saved tuning file
+decides where it was timed on the same kernels."""
 import numpy as np
 import pytest
 
@@ -50,3 +51,26 @@ def test_fp64_burn_takes_the_wider_mapping(zbm, opts):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     net.close()
+
+
+def test_tuning_file_of_other_kernels_applies_nothing(zbm, tmp_path):
+    """A saved file names the kernels it was timed on; one that names others, or none, leaves the
+    context's choices as they are."""
+    import json
+    zb, _ = zbm
+    a = zb.Context(0)
+    path = tmp_path / "tune.json"
+    zb.tune_save(a, path)
+    doc = json.loads(path.read_text())
+    doc["entries"] = [{"nv": 14, "nr": 30, "precision": 1, "lanes": 8, "auto_lanes": 8, "auto_lu": 0}]
+    net = zb.Network(a, W.nv14_network())
+    for kernels, applied in (("0" * 16, 0), (None, 0), (doc["kernels"], 1)):
+        other = {k: v for k, v in doc.items() if k != "kernels"}
+        if kernels:
+            other["kernels"] = kernels
+        path.write_text(json.dumps(other))
+        assert zb.get_mapping(a, net, "mixed") == 16
+        assert zb.tune_load(a, path) == applied
+    assert zb.get_mapping(a, net, "mixed") == 8
+    net.close()
+    a.close()
