@@ -129,6 +129,14 @@ extern "C" zb_err zb_context_destroy(zb_context *ctx)
 
 // ------------------------------------------------------------------ network
 
+// Whether some kernel that takes nv variables reads the consumed-reaction rows (DevNet::con).
+static bool reads_consumed(int nv)
+{
+    const KernelInfo *tab;
+    const int n = kernel_table(&tab);
+    return std::any_of(tab, tab + n, [&](const KernelInfo &k) { return k.nvp >= nv && jac_f32(k.nvp, k.mixed != 0); });
+}
+
 extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, zb_network **out)
 {
     if (!ctx || !d || !out) return fail(ZB_EINVAL, "NULL argument");
@@ -139,9 +147,8 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     if (nr < 0 || nr > RMAX) return fail(ZB_EINVAL, "n_reactions %d out of range 0..%d", nr, RMAX);
     if (nr > 0 && (!d->reactant || !d->product || !d->lnA || !d->n_exp || !d->E || (th && !d->q)))
         return fail(ZB_EINVAL, "NULL reaction array");
-    std::vector<int4> rct(std::max(nr, 1));
-    std::vector<unsigned> rab(std::max(nr, 1), 0u);   // packed as DevNet::rct
     std::vector<double4> par(std::max(nr, 1));
+    std::vector<double> qr(std::max(nr, 1));
     for (int r = 0; r < nr; ++r) {
         int a = d->reactant[2 * r], b = d->reactant[2 * r + 1];
         int c = d->product[2 * r], e = d->product[2 * r + 1];
@@ -150,50 +157,16 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
         double q = th ? d->q[r] : 0.0;
         if (!isfinite(d->lnA[r]) || !isfinite(d->n_exp[r]) || !isfinite(d->E[r]) || !isfinite(q))
             return fail(ZB_EINVAL, "reaction %d: non-finite parameter", r);
-        rct[r] = make_int4(a, b, c, e);
-        rab[r] = (unsigned)(8 * a) | ((unsigned)(8 * b) << 16);
         par[r] = make_double4(d->lnA[r], d->n_exp[r], d->E[r], q);
+        qr[r] = q;
     }
-    // per-species involvement lists (net stoichiometry != 0)
-    std::vector<std::vector<unsigned>> inv(ns);
-    for (int r = 0; r < nr; ++r) {
-        const int4 x = rct[r];
-        const unsigned cols = (unsigned)x.x << 16 | (unsigned)(x.y >= 0 ? x.y : x.x) << 22;
-        for (int i = 0; i < ns; ++i) {
-            int nu = (x.z == i) + (x.w == i) - (x.x == i) - (x.y == i);
-            if (nu != 0) inv[i].push_back((unsigned)(8 * r) | cols | ((unsigned)nu << 29));
-        }
-    }
-    int inv_len = 4;
-    for (int i = 0; i < ns; ++i) inv_len = std::max<int>(inv_len, (int)inv[i].size());
-    inv_len = (inv_len + 3) & ~3;   // the kernels take four entries per load
-    // padding: the 0 slot; room for the three loads the 14-row kernels make of every row
-    std::vector<unsigned> invf((size_t)ns * inv_len + 12, (unsigned)(8 * nr));
-    for (int i = 0; i < ns; ++i) std::copy(inv[i].begin(), inv[i].end(), invf.begin() + (size_t)i * inv_len);
-    // the reactions each species is a reactant of (DevNet::con)
-    std::vector<std::vector<std::pair<unsigned, double>>> con(ns);
-    for (int r0 = 0; r0 < nr; r0 += 64)
-        for (int side = 0; side < 2; ++side)
-            for (int r = r0; r < std::min(nr, r0 + 64); ++r) {
-                const int i = side ? rct[r].y : rct[r].x;
-                if (i >= 0) con[i].push_back({(unsigned)(8 * ((side + 1) * (nr + 1) + r)), par[r].w});
-            }
-    int con_len = 4;
-    for (int i = 0; i < ns; ++i) con_len = std::max<int>(con_len, (int)con[i].size());
-    con_len = (con_len + 3) & ~3;
-    std::vector<unsigned> conf((size_t)ns * con_len, (unsigned)(8 * nr));
-    std::vector<double> conq((size_t)ns * con_len, 0.0);
-    for (int i = 0; i < ns; ++i)
-        for (size_t e = 0; e < con[i].size(); ++e) {
-            conf[(size_t)i * con_len + e] = con[i][e].first;
-            conq[(size_t)i * con_len + e] = con[i][e].second;
-        }
+    const NetTables t = pack_network(ns, nr, d->reactant, d->product, qr.data(), th && reads_consumed(nv));
     // the parameters first: each table then starts on its own alignment (32, 16, 4 bytes)
     size_t o_par = 0, o_conq = o_par + sizeof(double4) * par.size();
-    size_t o_inv = o_conq + sizeof(double) * conq.size();
-    size_t o_con = o_inv + sizeof(unsigned) * invf.size();
-    size_t o_rct = o_con + sizeof(unsigned) * conf.size();
-    size_t bytes = o_rct + sizeof(unsigned) * rab.size();
+    size_t o_inv = o_conq + sizeof(double) * t.conq.size();
+    size_t o_con = o_inv + sizeof(unsigned) * t.inv.size();
+    size_t o_rct = o_con + sizeof(unsigned) * t.con.size();
+    size_t bytes = o_rct + sizeof(unsigned) * t.rct.size();
     zb_network *n = new (std::nothrow) zb_network();
     if (!n) return fail(ZB_ENOMEM, "host allocation failed");
     DeviceGuard g(ctx->device);
@@ -203,11 +176,11 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
         return fail(ZB_ENOMEM, "device allocation of %zu bytes failed", bytes);
     }
     std::vector<char> host(bytes);
-    memcpy(host.data() + o_rct, rab.data(), sizeof(unsigned) * rab.size());
-    memcpy(host.data() + o_par, par.data(), sizeof(double4) * par.size());
-    memcpy(host.data() + o_conq, conq.data(), sizeof(double) * conq.size());
-    memcpy(host.data() + o_con, conf.data(), sizeof(unsigned) * conf.size());
-    memcpy(host.data() + o_inv, invf.data(), sizeof(unsigned) * invf.size());
+    std::copy(par.begin(), par.end(), (double4 *)(host.data() + o_par));
+    std::copy(t.conq.begin(), t.conq.end(), (double *)(host.data() + o_conq));
+    std::copy(t.inv.begin(), t.inv.end(), (unsigned *)(host.data() + o_inv));
+    std::copy(t.con.begin(), t.con.end(), (unsigned *)(host.data() + o_con));
+    std::copy(t.rct.begin(), t.rct.end(), (unsigned *)(host.data() + o_rct));
     if (hipMemcpy(dm, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(dm);
         delete n;
@@ -219,11 +192,11 @@ extern "C" zb_err zb_network_create(zb_context *ctx, const zb_network_desc *d, z
     n->dn.nv = nv;
     n->dn.thermal = th;
     n->dn.nr = nr;
-    n->dn.inv_len = inv_len;
+    n->dn.inv_len = t.inv_len;
     n->dn.rct = (const unsigned *)(dm + o_rct);
     n->dn.par = (const double4 *)(dm + o_par);
     n->dn.inv = (const unsigned *)(dm + o_inv);
-    n->dn.con_len = con_len;
+    n->dn.con_len = t.con_len;
     n->dn.con = (const unsigned *)(dm + o_con);
     n->dn.conq = (const double *)(dm + o_conq);
     *out = n;

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "zb_internal.h"
+#include "zb_nettables.h"
 #include "zb_slots.h"
 #include "zb_tunecache.h"
 #include "zoneburn.h"

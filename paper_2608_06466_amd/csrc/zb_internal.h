@@ -25,7 +25,9 @@ constexpr int RMAX = 4096;   // largest number of reactions
 //              in the reaction columns (8 (nr + 1 + r) for reactant a, 8 (2 (nr + 1) + r)
 //              for b), conq[i][e] the reaction's q; rows padded with the 0 slot and q = 0 to
 //              con_len, a multiple of 4.  In the order in which 64 lanes that take the
-//              reactions in turn, a before b, come to the species.
+//              reactions in turn, a before b, come to the species.  Only for networks that
+//              kernels with FP32 Jacobian rows take, with temperature (else con_len = 0).
+// The packing is pack_network (zb_nettables.h).
 struct DevNet {
     int ns, nv, thermal, nr;
     int inv_len;
