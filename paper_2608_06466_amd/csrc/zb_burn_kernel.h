@@ -251,12 +251,12 @@ __device__ __forceinline__ T wave_pick(T v, bool flag)
 }
 
 // Value of lane K of the group (K a constant), in every lane of the group, without LDS:
-// quad_perm for L <= 4, row_newbcast (gfx90a+) within 16-lane rows, a permlane16 swap
-// between the two rows of a 32-lane group, v_readlane for a whole wave.
+// quad_perm for L <= 4, row_newbcast (gfx90a+) within 16-lane rows.  (Wider groups keep their
+// broadcasts within 16-lane rows too, lu_kept_spread and tri_solve.)
 template <int L, int K>
 __device__ __forceinline__ unsigned bcast_k32(unsigned v)
 {
-    static_assert(K >= 0 && K < L, "lane out of the group");
+    static_assert(L <= 16 && K >= 0 && K < L, "lane out of the group");
     if constexpr (L == 1) {
         return v;
     } else if constexpr (L == 2) {
@@ -266,14 +266,8 @@ __device__ __forceinline__ unsigned bcast_k32(unsigned v)
     } else if constexpr (L == 8) {
         unsigned a = (unsigned)dpp_i<0x150 + K>((int)v), b = (unsigned)dpp_i<0x158 + K>((int)v);
         return (threadIdx.x & 8) ? b : a;
-    } else if constexpr (L == 16) {
-        return (unsigned)dpp_i<0x150 + K>((int)v);
-    } else if constexpr (L == 32) {
-        unsigned a = (unsigned)dpp_i<0x150 + (K & 15)>((int)v), r0, r1;
-        xswap<16>(a, r0, r1);   // r0: the even row's value, r1: the odd row's, in both rows
-        return K < 16 ? r0 : r1;
     } else {
-        return (unsigned)__builtin_amdgcn_readlane((int)v, K);
+        return (unsigned)dpp_i<0x150 + K>((int)v);
     }
 }
 
@@ -1717,35 +1711,38 @@ __device__ __forceinline__ bool lu_kept_spread(const Ctx &c, Zone<NVP, L, LT> &z
 template <int NVP, int L, class LT>
 __device__ __forceinline__ bool lu_kept_order(const Ctx &c, Zone<NVP, L, LT> &z)
 {
-    if constexpr (L >= 32) return lu_kept_spread(c, z);
-    const int nv = own_copy(c.nv);
-    bool bad = false;
-    steps8<NVP>(nv, [&](auto K) {
-        constexpr int k = K;
-        const LT piv = bcast_k<L, k>(z.M[0][k]);
-        if constexpr (L == 16) {
-            const bool gt = lane_in(group_lanes<L>((0xFFFEull << k) & 0xFFFFull));
-            const bool ge = lane_in(group_lanes<L>((0xFFFFull << k) & 0xFFFFull));
-            bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
-            const LT rinv = recip(piv);
-            if (lane_in(group_lanes<L>(1ull << k))) z.dinv[0] = rinv;
-            LT l = z.M[0][k] * rinv;
-            l = gt ? l : LT(0);
-            z.M[0][k] = ge ? l : z.M[0][k];   // the pivot's own place is 0 (tri_solve)
-            row_update<k, true, 0, NVP - 1 - k, 4>(z.M[0], z.M[0], z.M[0] + k + 1, z.M[0] + k + 1, l);
-            return;
-        }
-        // each candidate against the pivot in its own lane, so no reduction per step: the
-        // rows of lanes below k are eliminated, lanes past nvp hold zero rows (a NaN fails)
-        const bool gt = lane_in(lanes_in<L>(0, L - 1) & ~lanes_in<L>(0, k));
-        bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
-        const LT rinv = recip(piv);
-        if (lane_in(lanes_in<L>(k, k))) z.dinv[0] = rinv;
-        const LT l = gt ? z.M[0][k] * rinv : LT(0);
-        if (gt) z.M[0][k] = l;
-        sfor<k + 1, NVP>([&](auto J) { z.M[0][J] = fma(-l, bcast_k<L, k>(z.M[0][J]), z.M[0][J]); });
-    });
-    return !gany<L>(bad);
+    if constexpr (L >= 32) {
+        return lu_kept_spread(c, z);
+    } else {
+        const int nv = own_copy(c.nv);
+        bool bad = false;
+        steps8<NVP>(nv, [&](auto K) {
+            constexpr int k = K;
+            const LT piv = bcast_k<L, k>(z.M[0][k]);
+            // each candidate against the pivot in its own lane, so no reduction per step: the
+            // rows of lanes below k are eliminated, lanes past nvp hold zero rows (a NaN fails)
+            if constexpr (L == 16) {
+                const bool gt = lane_in(group_lanes<L>((0xFFFEull << k) & 0xFFFFull));
+                const bool ge = lane_in(group_lanes<L>((0xFFFFull << k) & 0xFFFFull));
+                bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
+                const LT rinv = recip(piv);
+                if (lane_in(group_lanes<L>(1ull << k))) z.dinv[0] = rinv;
+                LT l = z.M[0][k] * rinv;
+                l = gt ? l : LT(0);
+                z.M[0][k] = ge ? l : z.M[0][k];   // the pivot's own place is 0 (tri_solve)
+                row_update<k, true, 0, NVP - 1 - k, 4>(z.M[0], z.M[0], z.M[0] + k + 1, z.M[0] + k + 1, l);
+            } else {
+                const bool gt = lane_in(lanes_in<L>(0, L - 1) & ~lanes_in<L>(0, k));
+                bad = bad || (gt && !(fabs(z.M[0][k]) <= fabs(piv) * LT(1.0f / PIV_KEEP)));
+                const LT rinv = recip(piv);
+                if (lane_in(lanes_in<L>(k, k))) z.dinv[0] = rinv;
+                const LT l = gt ? z.M[0][k] * rinv : LT(0);
+                if (gt) z.M[0][k] = l;
+                sfor<k + 1, NVP>([&](auto J) { z.M[0][J] = fma(-l, bcast_k<L, k>(z.M[0][J]), z.M[0][J]); });
+            }
+        });
+        return !gany<L>(bad);
+    }
 }
 
 // M = I - gamma J and its LU factors: in the kept pivot order where the kernel keeps one,
