@@ -40,9 +40,11 @@ FLAGS = [
 
 # Machine-scheduler strategy per kernel class, as measured: the 16-, 22-, 24- and 32-row kernels
 # run 1-3 % faster with max-ilp, the 48-row ones 5-9 % faster with iterative-ilp; the small
-# kernels keep the default, and so do the 14-row ones bound to three waves a SIMD (2^18 zones
-# mixed 428 ms, 437 with max-ilp; FP64, 50021 zones, 97.4 and 99.0; reuse, 30011 zones, 59.0 and
-# 62.3; their variable form without reuse, two waves, keeps max-ilp: 59.1 against 60.0).
+# kernels keep the default, and so do the 14-row ones but for their variable form without reuse.
+# Default and max-ilp on 14 variables, 100003 zones: reuse mixed 166 and 174 ms, FP64 189.1 and
+# 190.2; variable form with reuse mixed 210 and 218, FP64 223 and 225; without reuse mixed 237.4
+# and 238.6, FP64 239.3 and 236.8; every step, 2^18 zones mixed 428 and 437, 50021 zones FP64 97.4
+# and 99.0.
 SCHED = {
     **{f: "max-ilp" for f in ("zb_k16.hip", "zb_k14v.hip", "zb_k22.hip", "zb_k22r.hip", "zb_k16r.hip", "zb_k16n.hip", "zb_k24.hip",
                               "zb_k24r.hip", "zb_k32.hip", "zb_k32r.hip", "zb_kv_b.hip",

@@ -2623,7 +2623,8 @@ constexpr int min_waves_per_eu()
     // copy in registers.  FP64 (148 bytes a lane spilled; 214 VGPRs unbounded): 50021 zones 115 ->
     // 103 ms, 100003 of the 20-reaction network 62.6 -> 56.5; 512 zones, one wave a SIMD, 17.2 ->
     // 18.8.  The mixed reuse kernels too: 11 % faster (fixed-coefficient form) and 2 %
-    // (variable-coefficient form).  Measured slower with a third wave: the variable form with a
+    // (variable-coefficient form), as the kernels were before the DPP solves; they spill 268 and
+    // 304 bytes a lane, which costs 2.1 and 2.9 TB/s of scratch traffic.  Measured slower with a third wave: the variable form with a
     // Jacobian every step (60 -> 66 ms FP64), the 22-row FP64 kernel (82 -> 85 ms)
     if (NVP == 14 && L == 16 &&
         (JP == METHOD_BDF ||
